@@ -11,6 +11,7 @@ constexpr int kBq = 32;      // query rows per decision tile = rows of one wavef
 constexpr int kBk = 32;      // keys per decision tile
 constexpr int kDecBk = 32;   // keys per decode decision tile
 
+constexpr int kNumCus = 256;                 // compute units of an MI355X
 constexpr int kFwdWaves = 8;                 // wavefronts per forward workgroup (2 per SIMD)
 constexpr int kFwdRows = kFwdWaves * kBq;    // 256 query rows per workgroup
 constexpr int kDqWaves = 8;                  // wavefronts per dQ workgroup (2 per SIMD)

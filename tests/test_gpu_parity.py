@@ -993,6 +993,33 @@ def test_decode_bf16_output():
     assert torch.equal(b["o"], a["o"].to(torch.bfloat16)) and torch.equal(b["lse"], a["lse"])
 
 
+# (B, Hq, Hkv, Nq, Nk, D, taus): the forward of few row blocks runs another kernel unless
+# the counters are requested; sizes at its tile, stage (128 keys) and grid limits
+SMALL_GRID_FWD = [(1, 1, 1, 1, 129, 64), (1, 2, 1, 33, 128, 128), (1, 2, 1, 31, 160, 128),
+                  (2, 4, 2, 257, 257, 64), (1, 8, 2, 500, 2049, 128), (1, 8, 2, 1025, 1025, 128),
+                  (1, 2, 2, 128, 4100, 64)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Nq,Nk,D", SMALL_GRID_FWD)
+def test_small_grid_forward_gives_the_same_bits(B, Hq, Hkv, Nq, Nk, D):
+    # The kernel for few row blocks keeps the order of every sum and decision of the
+    # other one, so O, LSE and the row counts are the same bits.  Tolerances of 1e3 and
+    # more skip tiles that would have moved a row's softmax reference, after which P is
+    # formed again.
+    for tau, beta in ((0.0, 2.0), (1e-3, 6.0), (1.0, 2.0), (3e3, 0.8), (1e6, 1.0), (1e30, 1.0)):
+        w = Workload(dict(kind="train", B=B, Hq=Hq, Hkv=Hkv, N=Nk, D=D, beta=beta, local=0.5))
+        t = w.tensors(with_do=False)
+        q = dev(np.ascontiguousarray(t["q"][:, :, Nk - Nq:]))
+        k, v, s = dev(t["k"]), dev(t["v"]), f32(w.scale)
+        a = mala.fwd(q, k, v, s, tau)
+        o, lse = torch.full_like(a["o"], 7.0), torch.full_like(a["lse"], 7.0)
+        rt = torch.full_like(a["row_tiles"], -7)
+        mala.mala_fwd(q, k, v, o, lse, rt, None, s, tau)
+        torch.cuda.synchronize()
+        for name, x, y in (("o", a["o"], o), ("lse", a["lse"], lse), ("row_tiles", a["row_tiles"], rt)):
+            assert torch.equal(x, y), (tau, name)
+
+
 def test_concurrent_streams_match_sequential():
     # the library keeps no device state between calls: two forward + backward calls
     # on two streams at once give the results of the calls run one after the other
