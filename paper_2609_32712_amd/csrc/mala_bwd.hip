@@ -25,6 +25,8 @@
 // offline test as a check; role 1 accumulates dV one tile later and moves the query
 // tiles into LDS; role 2 forms dP and dS; role 3 accumulates dK two tiles later (dS
 // handed on as bf16 operands).
+// mala_bwd_dkdv_pairs_kernel does the same for 32 keys per workgroup and two query tiles
+// per step, for grids of few key blocks and sequences that retain few tiles (dkdv_rule).
 // On small grids the sweeps run in parts whose sums mala_bwd_dkdv_reduce_kernel
 // adds.  An MFMA with its operands exchanged gives the transposed scores bit for
 // bit, so both kernels see the same scores.
@@ -262,6 +264,9 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   const int it0 = part * p.psize, it1 = min(total, it0 + p.psize);
   if (it0 >= total) return;
   const float budget_share = 1.f / (float)((total + p.psize - 1) / p.psize);
+  if (p.by_sequence &&
+      sparse_sequence<1024>(p, nqt, off, mask_row0(p, b, sg), reinterpret_cast<longlong2*>(Qs)))
+    return;
   if (p.counters) blk_init(bcnt);
 
   // Query tiles are swept from the last one down to the block's diagonal, the
@@ -483,12 +488,16 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
             }
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) dpd = mfma32(oa[kk], kv[kk], dpd);
-            float ds[16];
+            float pv[16], dd[16], ds[16];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               const f32x4 p4 = Pf[t & 1][grp_k][g][lane];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) ds[4 * g + e] = p4[e] * dpd[4 * g + e];
+              for (int e = 0; e < 4; ++e) {
+                pv[4 * g + e] = p4[e];
+                dd[4 * g + e] = dpd[4 * g + e];
+                ds[4 * g + e] = p4[e] * dpd[4 * g + e];
+              }
             }
             // dK runs this tile without dS's lo term while the key's sum of |dS| in
             // such tiles stays within kLoMassDk (for every key of the tile); a tile
@@ -500,15 +509,10 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
             const float fk_new = fdk + as_key;
             const bool with_lo = wave_any(fk_new > kLoMassDk * budget_share || as_key > kLoTileDk);
             if (!with_lo) fdk = fk_new;
-            bf16x8 xh[2], xl[2];
+            const bf16x8 xh[2] = {hi_bf16x8(ds), hi_bf16x8(ds + 8)};
             if (with_lo) {
-              split_bf16x8(ds, xh[0], xl[0]);
-              split_bf16x8(ds + 8, xh[1], xl[1]);
-              dSop[t & 1][grp_k][2][lane] = xl[0];
-              dSop[t & 1][grp_k][3][lane] = xl[1];
-            } else {
-              xh[0] = hi_bf16x8(ds);
-              xh[1] = hi_bf16x8(ds + 8);
+              dSop[t & 1][grp_k][2][lane] = lo_product_bf16x8(pv, dd, xh[0]);
+              dSop[t & 1][grp_k][3][lane] = lo_product_bf16x8(pv + 8, dd + 8, xh[1]);
             }
             dSop[t & 1][grp_k][0][lane] = xh[0];
             dSop[t & 1][grp_k][1][lane] = xh[1];
@@ -638,6 +642,351 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
     }
   }
   // every role ends here, after the same number of barriers
+  if (p.counters) blk_flush(bcnt, p.counters);
+}
+
+// The key-major pass by pairs of query tiles: one workgroup per 32 keys, which takes the
+// query tiles that retain those keys two at a time.  Every sum and decision is the kernel
+// above's, in its order: the same bits.
+//
+// The kernel above steps through the tiles that any of its four key groups retains, one at
+// a time, ~2750 cycles each: as long as its chain of roles takes, whichever groups take
+// part.  Where the sweeps are few or skewed (short sequences, an attention sink, tiles
+// skipped at tau = 1) that chain sets the time.  Here a step does two tiles of one key
+// group, and only retained ones, in two stages:
+//   * producers (wavefronts 0, 1; one tile each), step s: S and dP, P and dS, handed on
+//     through LDS as bf16 operands (hi and lo) with their sums over the tile;
+//   * consumers (wavefronts 2-5), step s + 1: the lo-term budgets in tile order, then
+//     dV^T += dO^T P and dK^T += Q^T dS of the two tiles in order, the columns of dV and dK
+//     shared out among them;
+//   * loaders (wavefronts 6, 7; one tile each), step s - 1: Q and dO into LDS, and the row
+//     vectors (loaded into registers a step before that).
+// A step takes ~1 us: 0.5 us per tile of a sweep's chain where the kernel above takes 1.14
+// (a backward of 8 heads x 4096 tokens, GQA 4:1, D = 128: 729 -> 395 us), though as much
+// work per CU takes ~1.7x as long when every tile of every group is retained.  Measured on
+// the way here, each with the kernel above's roles on one key group and one tile per step:
+// four wavefronts alone 10-15% faster than 128 keys per workgroup, with tiles staged three
+// steps ahead and the next tile's MFMAs under this one's vector work no more than that.
+template <int D>
+__global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
+  constexpr int KS = D / 16;       // k-steps over head_dim
+  constexpr int DB = D / 32;       // 32-wide column blocks
+  constexpr int RC = D / 8 + 1;                     // 16-byte chunk positions per LDS row
+  constexpr int NI = (kBq * RC + 63) / 64;          // 64-chunk LDS-DMA loads per tile
+  constexpr int TS = NI * 64 * 8;                   // tile slot stride (elements)
+  constexpr int CHUNK = 1024;                       // iterations compacted at once
+  constexpr int PER = CHUNK / 512;
+  constexpr int NM = DB == 4 ? 2 : 1;               // accumulators per consumer
+  // rings of three pairs: loading, producers, consumers
+  __shared__ __attribute__((aligned(16))) bf16 Qs[3][2][TS];
+  __shared__ __attribute__((aligned(16))) bf16 dOs[3][2][TS];
+  // hand-off of a tile: P hi0, hi1, lo0, lo1, dS hi0, hi1, lo0, lo1
+  __shared__ __attribute__((aligned(16))) bf16x8 hand[2][2][8][64];
+  __shared__ f32x2 sums[2][2][kBk];                 // per key: P mass and sum of |dS| of the tile
+  // per-row vectors: lse2, test threshold (written only when counters are requested), -D_q
+  __shared__ __attribute__((aligned(16))) float rowv[2][2][3][kBq];
+  __shared__ int2 plist[CHUNK];                     // processed tiles: query tile, head of the group
+  __shared__ int wsum[8];                           // per-wavefront counts of the compaction
+  __shared__ unsigned long long bcnt[kNumCounters];   // the workgroup's counter sums
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5, c = lane & 31, G = lane >> 4, t16 = lane & 15;
+  const int BHk = p.B * p.Hkv;
+  constexpr int NS = kBwdKeys / kBk;               // workgroups per block of 128 keys
+  const int part = blockIdx.x / (p.nkblk * BHk * NS);   // part of the sweep (split sweeps)
+  const int bhk = blockIdx.x % BHk;
+  const int kx = (blockIdx.x / BHk) % (p.nkblk * NS);   // ascending: the longest sweeps first
+  const int kblk = kx / NS, sub = kx % NS;
+  const int b = bhk / p.Hkv, hkv = bhk % p.Hkv, grp = p.Hq / p.Hkv;
+  const Seg sg = seq_slice(p, b);
+  const int Nq = sg.Nq, Nk = sg.Nk;
+  const long off = (long)Nk - Nq;
+  const int kb0 = kblk * kBwdKeys, kw = kb0 + sub * kBk;   // first key of the block / workgroup
+  if (kw >= Nk || Nq == 0) return;         // past the end of (or a skipped) packed sequence
+  const long kbase = sg.kb + (long)hkv * p.Nk;     // key 0 of this (sequence, KV head)
+  const int key = kw + c;                          // this lane's key (C-layout column)
+  const int nqt = (Nq + kBq - 1) / kBq;
+  // the iterations and parts are those of the block of 128 keys
+  const int total = dkdv_iterations(Nq, Nk, kb0, grp);
+  const int it0 = part * p.psize, it1 = min(total, it0 + p.psize);
+  if (it0 >= total) return;
+  const float budget_share = 1.f / (float)((total + p.psize - 1) / p.psize);
+  const int mrow0 = mask_row0(p, b, sg);
+  if (p.by_sequence && !sparse_sequence<512>(p, nqt, off, mrow0, reinterpret_cast<longlong2*>(Qs)))
+    return;
+  if (p.counters) blk_init(bcnt);
+
+  // The processed iterations of [c0, c0 + CHUNK) into plist, PER per thread, placed by a
+  // prefix sum; returns how many there are.
+  auto compact = [&](int c0) {
+    int np = 0, cnt = 0, bits = 0;
+    unsigned n_do = 0;   // statistics: dO tiles that some key group of the block retains
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int it = c0 + PER * tid + u;
+      const int dec = it < it1 ? (int)p.mask[mask_index(p, mrow0 + nqt - 1 - it / grp,
+                                                         hkv * grp + it % grp, kblk)] : 0;
+      n_do += dec != 0;
+      bits |= ((dec >> sub) & 1) << u;
+      cnt += (dec >> sub) & 1;
+    }
+    int x = cnt;   // inclusive scan over the wavefront
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(x, d);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    if (p.counters && sub == 0) {
+      blk_add(bcnt, kCntVTiles, n_do);
+      blk_add(bcnt, kCntVNeeded, n_do);
+    }
+    int pos = x - cnt;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      const int s_ = wsum[w];
+      pos += w < wave ? s_ : 0;
+      np += s_;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if ((bits >> u) & 1) {
+        const int it = c0 + PER * tid + u;
+        plist[pos++] = int2{nqt - 1 - it / grp, it % grp};
+      }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(np);
+  };
+
+  if (wave < 2) {
+    // producers
+    const int rdo = rd_base<D>(c, h);
+    bf16x8 kop[KS], vop[KS];   // K and V rows of this lane's key as B operands
+    {
+      const bf16* kp = p.k + (kbase + key) * D + 8 * h;
+      const bf16* vp = p.v + (kbase + key) * D + 8 * h;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {
+        kop[kk] = key < Nk ? load8(kp + 16 * kk) : zero8();
+        vop[kk] = key < Nk ? load8(vp + 16 * kk) : zero8();
+      }
+    }
+    unsigned n_ret_kv = 0;          // statistics: processed tiles whose test this pass confirms
+    unsigned long long hsum = 0;    // and their fingerprints
+    for (int c0 = it0; c0 < it1; c0 += CHUNK) {
+      const int np = compact(c0), S = (np + 1) / 2;
+      if (!np) continue;
+      for (int s = -2; s <= S; ++s) {
+        const int i = 2 * s + wave;
+        if (s >= 0 && i < np) {
+          const int2 e = plist[i];
+          const bf16* qr = lds_pin(&Qs[s % 3][wave][rdo]);
+          const bf16* orr = lds_pin(&dOs[s % 3][wave][rdo]);
+          const float* rv = &rowv[s & 1][wave][0][0];
+          bf16x8 qa[KS], oa[KS];
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) qa[kk] = load8(qr + rd_step<D>(kk));
+          // dP - D: the accumulator starts at -D of each row (C layout: register 4 g + e
+          // holds row 8 g + 4 h + e)
+          f32x16 dpd;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 d4 = *reinterpret_cast<const f32x4*>(rv + 2 * kBq + 8 * g + 4 * h);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dpd[4 * g + r] = d4[r];
+          }
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) oa[kk] = load8(orr + rd_step<D>(kk));
+          const f32x16 sc = qk_tile<KS>(qa, kop);
+          const int qt = __builtin_amdgcn_readfirstlane(e.x), q0 = qt * kBq;
+          const bool need_mask =
+              ((long)kw + kBk - 1 > (long)q0 + off) || (q0 + kBq > Nq) || (kw + kBk > Nk);
+          const int klo = key < Nk ? (int)((long)key - off - q0) - 4 * h : 1000000;
+          const int qlim = Nq - q0 - 4 * h;
+          float sv[16];
+          if (p.counters) {
+            // the offline test again, as a statistic: it confirms the dQ pass's decision
+            if (wave_any(offline_entries(sc, p.scale2, need_mask, klo, qlim, rv + kBq, h, sv))) {
+              ++n_ret_kv;
+              hsum += tile_hash(b, hkv * grp + __builtin_amdgcn_readfirstlane(e.y), qt, kw / kBk);
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sv[r] = sc[r];
+          if (need_mask) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                sv[4 * g + r] = (8 * g + r >= klo) && (8 * g + r < qlim) ? sc[4 * g + r] : kNegInf;
+          }
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) dpd = mfma32(oa[kk], vop[kk], dpd);
+          probabilities(sv, p.scale2, rv, h);
+          float ps = 0.f, as = 0.f, ds[16], dd[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ps += sv[r];
+          bf16x8 (&hd)[8][64] = hand[s & 1][wave];
+          const bf16x8 p0 = hi_bf16x8(sv), p1 = hi_bf16x8(sv + 8);
+          hd[0][lane] = p0;
+          hd[1][lane] = p1;
+          hd[2][lane] = lo_bf16x8(sv, p0);
+          hd[3][lane] = lo_bf16x8(sv + 8, p1);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            dd[r] = dpd[r];
+            ds[r] = sv[r] * dpd[r];
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) as += fabsf(ds[r]);
+          const bf16x8 d0 = hi_bf16x8(ds), d1 = hi_bf16x8(ds + 8);
+          hd[4][lane] = d0;
+          hd[5][lane] = d1;
+          hd[6][lane] = lo_product_bf16x8(sv, dd, d0);
+          hd[7][lane] = lo_product_bf16x8(sv + 8, dd + 8, d1);
+          const float pk = halves_sum(ps), ak = halves_sum(as);
+          if (h == 0) sums[s & 1][wave][c] = f32x2{pk, ak};
+        }
+        __syncthreads();
+      }
+    }
+    if (p.counters && lane == 0) {
+      blk_add(bcnt, kCntRetainedKV, n_ret_kv);
+      blk_add(bcnt, kCntSetHashKV, hsum);
+    }
+  } else if (wave < 6) {
+    // consumers: columns 32 db .. of dV and dK (D = 64: of one of the two)
+    const int x = wave - 2, db = x % DB, mat0 = NM == 2 ? 0 : x / DB;
+    const int tro = tr_base<D>(4 * h + (t16 >> 2), G & 1, t16) + 8 * db;
+    f32x16 acc[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+    float fdv = 0.f, fdk = 0.f;   // this key's P mass / sum of |dS| in tiles run without the lo term
+    for (int c0 = it0; c0 < it1; c0 += CHUNK) {
+      const int np = compact(c0), S = (np + 1) / 2;
+      if (!np) continue;
+      for (int s = -2; s <= S; ++s) {
+        const int t = s - 1;
+        if (t >= 0) {
+          bf16x8 a[2][NM][2], bo[2][NM][2];
+          f32x2 sm[2];
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {       // the second tile of an odd last pair: not used
+            sm[w] = sums[t & 1][w][c];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+              const int mat = mat0 + m;
+              const bf16* at = lds_pin((mat ? &Qs[t % 3][w][0] : &dOs[t % 3][w][0]) + tro);
+#pragma unroll
+              for (int ks = 0; ks < 2; ++ks) {
+                a[w][m][ks] = cat(lds_read_tr(at + 16 * ks * (D + 8)),
+                                  lds_read_tr(at + (16 * ks + 8) * (D + 8)));
+                bo[w][m][ks] = hand[t & 1][w][4 * mat + ks][lane];
+              }
+            }
+          }
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            if (2 * t + w >= np) continue;
+            // dV runs a tile without P's lo term while the key's P mass in such tiles stays
+            // within kLoMassDv (for every key of the tile); dK likewise with |dS|, and a tile
+            // holding more than kLoTileDk of some key's |dS| always takes the lo term
+            const float fv_new = fdv + sm[w][0], fk_new = fdk + sm[w][1];
+            const bool lo_v = wave_any(fv_new > kLoMassDv * budget_share);
+            const bool lo_k = wave_any(fk_new > kLoMassDk * budget_share || sm[w][1] > kLoTileDk);
+            if (!lo_v) fdv = fv_new;
+            if (!lo_k) fdk = fk_new;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+              const int mat = mat0 + m;
+              acc[m] = mfma32(a[w][m][0], bo[w][m][0], acc[m]);
+              acc[m] = mfma32(a[w][m][1], bo[w][m][1], acc[m]);
+              if (mat ? lo_k : lo_v) {
+                acc[m] = mfma32(a[w][m][0], hand[t & 1][w][4 * mat + 2][lane], acc[m]);
+                acc[m] = mfma32(a[w][m][1], hand[t & 1][w][4 * mat + 3][lane], acc[m]);
+              }
+            }
+          }
+        }
+        __syncthreads();
+      }
+    }
+    // dV = sum P^T dO, dK = scale * sum dS^T Q; lane (h, c) holds key kw + c
+    // (split sweeps: this part's fp32 sums to its slots of the partial buffer)
+    if (key < Nk) {
+      const bool split = p.nparts > 1;
+      const long krow = (kbase + key) * D + 32 * db + 4 * h;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const int mat = mat0 + m;
+        const float f = mat ? p.scale : 1.f;
+        void* dst = split ? (void*)(p.part + (size_t)(2 * part + mat) *
+                                                 ((size_t)p.B * p.Hkv * p.Nk) * D)
+                          : (mat ? p.dk : p.dv);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          store_out4(dst, krow + 8 * g,
+                     f32x4{acc[m][4 * g] * f, acc[m][4 * g + 1] * f, acc[m][4 * g + 2] * f,
+                           acc[m][4 * g + 3] * f}, split ? 0 : p.grad_bf16);
+      }
+    }
+  } else {
+    // loaders
+    const int w = wave - 6;
+    uint32_t dma_off[NI];
+#pragma unroll
+    for (int u = 0; u < NI; ++u) dma_off[u] = dma_lane_offset<D>(64 * u + lane);
+    float plse = 0.f, pdv = 0.f;   // row c of tile h of the pair two steps on (the first loader)
+    int pq = 0;                    // and its row number
+    for (int c0 = it0; c0 < it1; c0 += CHUNK) {
+      const int np = compact(c0), S = (np + 1) / 2;
+      if (!np) continue;
+      for (int s = -2; s <= S; ++s) {
+        if (s >= -1 && s + 1 < S) {
+          if (w == 0) {
+            // the same arithmetic as row_vectors (the query-major kernel must agree bitwise)
+#pragma clang fp contract(off)
+            const bool prow = pq < Nq;
+            const float l2 = plse * kLog2e;
+            float (&rv)[3][kBq] = rowv[(s + 1) & 1][h];
+            rv[0][c] = prow ? l2 : 0.f;
+            if (p.counters) {   // the threshold feeds only the statistics' re-run of the test
+              const float plg = log2f((float)((long)pq + 1 + off));
+              rv[1][c] = prow ? l2 + p.log2tau - plg : __builtin_huge_valf();
+            }
+            rv[2][c] = prow ? -pdv : 0.f;
+          }
+          const int i = 2 * (s + 1) + w;
+          if (i < np) {
+            const int2 e = plist[i];
+            const int q0 = __builtin_amdgcn_readfirstlane(e.x) * kBq;
+            const long r0 = sg.qb + (long)(hkv * grp + __builtin_amdgcn_readfirstlane(e.y)) * p.Nq + q0;
+            const uint32_t nb = (uint32_t)(Nq - q0) * (uint32_t)D * 2u;
+            const i32x4 rq = rsrc_words(p.q + r0 * D, nb), ro = rsrc_words(p.dout + r0 * D, nb);
+            const int slot = (s + 1) % 3;
+#pragma unroll
+            for (int u = 0; u < NI; ++u) buf_load_lds16(rq, dma_off[u], &Qs[slot][w][512 * u]);
+#pragma unroll
+            for (int u = 0; u < NI; ++u) buf_load_lds16(ro, dma_off[u], &dOs[slot][w][512 * u]);
+          }
+        }
+        if (w == 0 && s + 2 < S) {
+          const int2 e = plist[min(2 * (s + 2) + h, np - 1)];
+          pq = e.x * kBq + c;
+          const long r = sg.qb + (long)(hkv * grp + e.y) * p.Nq + min(pq, Nq - 1);
+          plse = p.lse[r];
+          pdv = p.dvec[r];
+        }
+        wait_vm();
+        __syncthreads();
+      }
+    }
+  }
+  // every wavefront ends here, after the same number of barriers
   if (p.counters) blk_flush(bcnt, p.counters);
 }
 
@@ -937,21 +1286,50 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
   }
 }
 
-hipError_t launch_bwd(const BwdParams& p, int D, hipStream_t st) {
-  dim3 grid_kv((unsigned)p.nkblk * p.B * p.Hkv * p.nparts), block_kv(1024);
+// The dK/dV kernel of a call.  n: sweeps of 128-key blocks (or their parts).  Where they
+// leave CUs idle the chain of a sweep sets the time and the pairs kernel takes all (n <=
+// 256; us per backward, other kernel / pairs, tau = 1e-3: 8 heads GQA 4:1 D = 128, n = 16
+// (1024 tokens) 211 / 117, n = 64 (4096 tokens) 729 / 395, n = 256 (4 x 4096) 797 / 760; 2 x
+// 4 heads x 700 tokens 104 / 69; MHA 8 heads x 4096, D = 64, n = 256 265 / 251).  Above,
+// where every tile is retained the other kernel is ahead (n = 512: 463 / 564, n = 1024: 1194
+// / 1541), so the pairs take sequences that skip, which a tolerance below 0.1 does not
+// promise.  Both kernels are then launched and one of them leaves at once, at ~1.2 us per
+// workgroup: under 2% of sweeps of 512 iterations and more.  8 x 4096 language-model-like
+// tokens at tau = 1: 872 / 522.
+enum class DkdvRule { kPairs, kBlocks, kBySequence };
+static DkdvRule dkdv_rule(const BwdParams& p) {
+  long n = (long)p.nkblk * p.B * p.Hkv;
+  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B));
+  n *= p.nparts;
+  if (n <= kNumCus) return DkdvRule::kPairs;
+  const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
+  return p.log2tau >= -3.33f && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
+}
+
+template <int D>
+static void launch_bwd_t(BwdParams p, hipStream_t st) {
   dim3 grid_q((unsigned)p.nqblk * p.B * p.Hq), block_q(kDqWaves * 64);
-  const long n4 = (long)p.B * p.Hkv * p.Nk * (D / 4);
-  dim3 grid_r((unsigned)std::min<long>((n4 + 255) / 256, 8192));
+  const unsigned n = (unsigned)p.nkblk * p.B * p.Hkv * p.nparts;   // 128-key sweeps
+  const DkdvRule rule = dkdv_rule(p);
+  p.by_sequence = rule == DkdvRule::kBySequence;
   // the dQ pass first: it records the tile decisions that the key-major pass follows
-  if (D == 128) {
-    hipLaunchKernelGGL(mala_bwd_dq_kernel<128>, grid_q, block_q, 0, st, p);
-    hipLaunchKernelGGL(mala_bwd_dkdv_kernel<128>, grid_kv, block_kv, 0, st, p);
-    if (p.nparts > 1) hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<128>, grid_r, dim3(256), 0, st, p);
-  } else {
-    hipLaunchKernelGGL(mala_bwd_dq_kernel<64>, grid_q, block_q, 0, st, p);
-    hipLaunchKernelGGL(mala_bwd_dkdv_kernel<64>, grid_kv, block_kv, 0, st, p);
-    if (p.nparts > 1) hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<64>, grid_r, dim3(256), 0, st, p);
+  hipLaunchKernelGGL(mala_bwd_dq_kernel<D>, grid_q, block_q, 0, st, p);
+  if (rule != DkdvRule::kPairs)
+    hipLaunchKernelGGL(mala_bwd_dkdv_kernel<D>, dim3(n), dim3(1024), 0, st, p);
+  if (rule != DkdvRule::kBlocks)
+    hipLaunchKernelGGL(mala_bwd_dkdv_pairs_kernel<D>, dim3(4 * n), dim3(512), 0, st, p);
+  if (p.nparts > 1) {
+    const long n4 = (long)p.B * p.Hkv * p.Nk * (D / 4);
+    hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<D>,
+                       dim3((unsigned)std::min<long>((n4 + 255) / 256, 8192)), dim3(256), 0, st, p);
   }
+}
+
+hipError_t launch_bwd(const BwdParams& p, int D, hipStream_t st) {
+  if (D == 128)
+    launch_bwd_t<128>(p, st);
+  else
+    launch_bwd_t<64>(p, st);
   return hipGetLastError();
 }
 

@@ -1020,6 +1020,35 @@ def test_small_grid_forward_gives_the_same_bits(B, Hq, Hkv, Nq, Nk, D):
             assert torch.equal(x, y), (tau, name)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,tau,needle_block", [
+    (33, 2, 2, 500, 64, 1e-3, 1), (17, 4, 2, 1025, 128, 1e-3, 1), (17, 4, 2, 993, 128, 1.0, 32),
+    (129, 2, 1, 129, 128, 0.0, 1), (5, 8, 2, 4065, 128, 1.0, 32), (5, 8, 2, 4096, 64, 1.0, 1),
+    (17, 4, 2, 1000, 64, 1e30, 1)])
+def test_key_major_kernels_give_the_same_bits(B, Hq, Hkv, N, D, tau, needle_block):
+    # A batch of one has few key blocks and takes the kernel of query-tile pairs; the
+    # same sequence in a batch with more than 256 key blocks takes the kernel of
+    # 128-key blocks, or at tau = 1 and long sweeps whichever its decisions call for
+    # (sparse ones stay with the pairs).  Gradients and statistics must not show it.
+    w = Workload(dict(kind="train", B=1, Hq=Hq, Hkv=Hkv, N=N, D=D, beta=2.0, local=2.0,
+                      needle_block=needle_block, sink=1.5 if needle_block > 1 else 0.0))
+    assert -(-N // 128) * Hkv <= 256 < -(-N // 128) * Hkv * B
+    t = w.tensors()
+    x = [dev(t[n]) for n in ("q", "k", "v", "do")]
+    many = [a.expand(B, -1, -1, -1).contiguous() for a in x]
+    s = f32(w.scale)
+    f1, fb = (mala.fwd(*a[:3], s, tau) for a in (x, many))
+    b1, bb = (mala.bwd(*a[:3], f["o"], f["lse"], a[3], s, tau) for a, f in ((x, f1), (many, fb)))
+    torch.cuda.synchronize()
+    for name in ("dq", "dk", "dv", "row_tiles"):
+        for b in (0, B - 1):
+            assert torch.equal(b1[name][0], bb[name][b]), (name, b)
+    c1, cb = counters(b1["counters"]), counters(bb["counters"])
+    for i in (mala.CNT_RETAINED, mala.CNT_RETAINED_KV, mala.CNT_V_TILES, mala.CNT_V_NEEDED):
+        assert cb[i] == B * c1[i], i
+    _check_backward_passes_agree(c1)
+    _check_backward_passes_agree(cb)
+
+
 def test_concurrent_streams_match_sequential():
     # the library keeps no device state between calls: two forward + backward calls
     # on two streams at once give the results of the calls run one after the other
