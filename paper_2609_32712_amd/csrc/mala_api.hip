@@ -253,7 +253,7 @@ int check_decode(const void* q, const void* k_cache, const void* v_cache, const 
 
 // The split kernel writes every partial [B, Hq, num_splits, D + 4] (also for splits
 // without tiles: o = 0, lse = -inf) before the merge kernel reads it, so the buffer
-// needs no clearing.
+// needs no clearing; with one split it writes the outputs themselves.
 int run_decode(const void* q, const void* k_cache, const void* v_cache, const int32_t* cache_lens,
                void* o, float* lse, int32_t* head_tiles, int64_t* counters, int num_splits,
                float* part, int B, int Hq, int Hkv, int Nk, int D, float scale, float tau,
@@ -278,10 +278,11 @@ int run_decode(const void* q, const void* k_cache, const void* v_cache, const in
   p.scale2 = scale * mala::kLog2e;
   p.thr2 = log2_tau(tau) - log2f((float)Nk);
   p.log2tau = log2_tau(tau);
-  if ((e = mala::launch_decode(p, D, s)) != hipSuccess) return hip_fail(e, "mala_decode: split launch");
-  if ((e = mala::launch_decode_combine(part, o, out_dtype == MALA_OUT_BF16, lse, head_tiles,
-                                       B * Hq, num_splits, D, s)) != hipSuccess)
-    return hip_fail(e, "mala_decode: combine launch");
+  p.o = o;
+  p.o_bf16 = out_dtype == MALA_OUT_BF16;
+  p.lse = lse;
+  p.head_tiles = head_tiles;
+  if ((e = mala::launch_decode(p, D, s)) != hipSuccess) return hip_fail(e, "mala_decode: kernel launch");
   return MALA_OK;
 }
 

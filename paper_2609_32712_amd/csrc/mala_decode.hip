@@ -28,11 +28,42 @@
 // branch, the compiler's waits count exactly the loads a step needs, so the next
 // K tile and the next V tile stay in flight while a tile is processed.
 // Partials (O / l, lse, count) go to the workspace; a second kernel merges the
-// splits with the normalizer-aware (log-sum-exp weighted) reduction.
+// splits with the normalizer-aware (log-sum-exp weighted) reduction.  With one split the
+// outputs are written at once.  Calls of few splits run a team of wavefronts per split
+// (mala_decode_team_kernel).
 #include "mala_device.h"
 #include "mala_kernels.h"
 
 namespace mala {
+
+// The result of split s for head bh (of lane group g's columns): O / l, lse (natural log)
+// and the retained-tile count, as a partial, or as the outputs when there is one split.  A
+// split without tiles has l = 0 (o = 0, lse = -inf: the merge skips it); a NaN or Inf input
+// leaves l NaN, which must reach the merge as NaN, not as an empty split.
+template <int D>
+__device__ __forceinline__ void write_split(const DecParams& p, long bh, int s, int g,
+                                            const f32x4 (&acc)[D / 16], float m, float l, int cnt) {
+  const float inv = l != 0.f ? 1.f / l : 0.f;
+  const float lse = l != 0.f ? (m + fast_log2(l)) * kLn2 : kNegInf;
+  if (p.S == 1) {
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db)
+      store_out4(p.o, bh * D + 16 * db + 4 * g, acc[db] * inv, p.o_bf16);
+    if (g == 0) {
+      p.lse[bh] = lse;
+      if (p.head_tiles) p.head_tiles[bh] = cnt;
+    }
+    return;
+  }
+  float* pp = p.part + (bh * p.S + s) * (D + kDecStride);
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db)
+    *reinterpret_cast<f32x4*>(pp + 16 * db + 4 * g) = acc[db] * inv;
+  if (g == 0) {
+    pp[D] = lse;
+    pp[D + 1] = __int_as_float(cnt);
+  }
+}
 
 template <int D>
 __global__ __launch_bounds__(64) void mala_decode_split_kernel(DecParams p) {
@@ -199,20 +230,7 @@ __global__ __launch_bounds__(64) void mala_decode_split_kernel(DecParams p) {
     mt = mtn;
   }
 
-  // partial of this split: O / l, lse (natural log) and the retained-tile count.  A
-  // split without tiles has l = 0 (o = 0, lse = -inf: the merge skips it); a NaN or
-  // Inf input leaves l NaN, which must reach the merge as NaN, not as an empty split.
-  float* pp = p.part + (((long)b * p.Hq + hq) * p.S + s) * (D + kDecStride);
-  if (head_valid) {
-    const float inv = l != 0.f ? 1.f / l : 0.f;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-      *reinterpret_cast<f32x4*>(pp + 16 * db + 4 * g) = acc[db] * inv;
-    if (g == 0) {
-      pp[D] = l != 0.f ? (m + fast_log2(l)) * kLn2 : kNegInf;
-      pp[D + 1] = __int_as_float(cnt);
-    }
-  }
+  if (head_valid) write_split<D>(p, (long)b * p.Hq + hq, s, g, acc, m, l, cnt);
   if (p.counters) {
     if (head_valid && g == 0 && cnt) {
       atomicAdd(&p.counters[kCntRetained], (unsigned long long)cnt);
@@ -223,6 +241,195 @@ __global__ __launch_bounds__(64) void mala_decode_split_kernel(DecParams p) {
       atomicAdd(&p.counters[kCntLegal], (unsigned long long)(t_hi > t_lo ? t_hi - t_lo : 0) * nh);
       if (vfetch) atomicAdd(&p.counters[kCntVTiles], (unsigned long long)vfetch);
       if (vloads) atomicAdd(&p.counters[kCntVNeeded], (unsigned long long)vloads);
+    }
+  }
+}
+
+// Decode of few splits: W wavefronts per split, a key tile each, so that calls whose splits
+// do not fill the chip (one sequence, few heads, short caches) read and score W tiles of a
+// split at once.  What bounds such a call is the latency of a split's chain of tiles (~1.2
+// us each for the kernel above); only the test is serial.  Per round of W tiles, from the
+// last one down: every wavefront scores its tile and publishes the tile's maximum and sum
+// per head (reference: that maximum); barrier; every wavefront takes the W tests in order,
+// carrying (m, l) of the split; a wavefront whose tile some head retains accumulates its
+// P V against a reference of its own (the largest maximum of its retained tiles).  The W
+// accumulators are brought to the split's reference and added at the end.  K and V of the
+// next round load while a round is worked on; V is fetched for every tile.
+template <int D, int W>
+__global__ __launch_bounds__(W * 64) void mala_decode_team_kernel(DecParams p) {
+  constexpr int KS = D / 32;   // k-steps of 32 over head_dim
+  constexpr int NDB = D / 16;  // 16-row blocks of O^T
+  constexpr int LD = D + 8;
+  constexpr int VCH = kDecBk * D / 8 / 64;   // 16-byte chunks per lane per tile
+  __shared__ __attribute__((aligned(16))) bf16 Ks[W][kDecBk * LD];
+  __shared__ __attribute__((aligned(16))) bf16 Vs[W][kDecBk * LD];
+  __shared__ f32x2 red[2][W][16];            // per tile and head: maximum, sum
+  __shared__ float refs[W][16];              // the wavefronts' references at the end
+
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = blockIdx.x % p.S;
+  const int chunk = (blockIdx.x / p.S) % p.nchunk;     // heads 16 chunk .. 16 chunk + 15
+  const int bhk = blockIdx.x / p.S / p.nchunk;
+  const int b = bhk / p.Hkv, hkv = bhk % p.Hkv, grp = p.Hq / p.Hkv;
+  const int nh = min(16, grp - 16 * chunk);             // query heads of this workgroup
+  int n = p.Nk, T = p.T, tps = p.tps;
+  float thr2 = p.thr2;
+  if (p.lens) {
+    n = min(max(p.lens[b], 0), p.Nk);
+    T = (n + kDecBk - 1) / kDecBk;
+    tps = (T + p.S - 1) / p.S;
+    thr2 = p.log2tau - log2f((float)n);   // L = n (n = 0 leaves no tile to test)
+  }
+  const int t_lo = s * tps, t_hi = min(T, t_lo + tps);
+  const bool head_valid = col < nh;
+  const int hq = hkv * grp + 16 * chunk + col;
+  const bf16* Kp = p.k + (long)bhk * p.Nk * D;
+  const bf16* Vp = p.v + (long)bhk * p.Nk * D;
+
+  // tile rows at or past n, and tiles outside the split, read as zeros
+  bf16x8 kr[VCH], vr[VCH];
+  auto load = [&](const bf16* base, int t, bf16x8 (&x)[VCH]) {
+    const long k0 = (long)max(t, 0) * kDecBk;
+    const long rows = t >= t_lo ? min((long)kDecBk, (long)n - k0) : 0;
+    const auto r = make_rsrc(base + k0 * D, (uint32_t)(rows > 0 ? rows * D * 2 : 0));
+#pragma unroll
+    for (int e = 0; e < VCH; ++e) x[e] = buf_load8_stream(r, 16u * (lane + 64 * e));
+  };
+  auto to_lds = [&](bf16* dst, const bf16x8 (&x)[VCH]) {
+#pragma unroll
+    for (int e = 0; e < VCH; ++e) {
+      const int ch = lane + 64 * e;
+      store8(dst + (ch / (D / 8)) * LD + (ch % (D / 8)) * 8, x[e]);
+    }
+  };
+  load(Kp, t_hi - 1 - w, kr);
+  load(Vp, t_hi - 1 - w, vr);
+  bf16x8 qreg[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk)
+    qreg[kk] = head_valid ? load8(p.q + ((long)b * p.Hq + hq) * D + 32 * kk + 8 * g) : zero8();
+
+  float m = kNegInf, l = 0.f;        // of the split
+  float ref = kNegInf;               // of this wavefront's accumulator
+  f32x4 acc[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int cnt = 0;
+  unsigned vloads = 0;               // V tiles consumed (statistics)
+  unsigned long long hsum = 0;       // fingerprints of this head's retained tiles
+
+  for (int t0 = t_hi - 1, round = 0; t0 >= t_lo; t0 -= W, ++round) {
+    const int t = t0 - w;
+    // the wavefront's LDS accesses complete in issue order: its reads below see the
+    // stores, the next round's stores follow the reads
+    to_lds(Ks[w], kr);
+    load(Kp, t - W, kr);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      s0 = mfma16(load8(Ks[w] + col * LD + 32 * kk + 8 * g), qreg[kk], s0);
+      s1 = mfma16(load8(Ks[w] + (16 + col) * LD + 32 * kk + 8 * g), qreg[kk], s1);
+    }
+    const long kb = (long)t * kDecBk;
+    float sv[8], mt = kNegInf;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float x0 = s0[r] * p.scale2, x1 = s1[r] * p.scale2;
+      if (kb + 4 * g + r >= n) x0 = kNegInf;
+      if (kb + 16 + 4 * g + r >= n) x1 = kNegInf;
+      sv[r] = x0;
+      sv[4 + r] = x1;
+      mt = fmaxf(mt, fmaxf(x0, x1));
+    }
+    mt = fmaxf(mt, __shfl_xor(mt, 16));
+    mt = fmaxf(mt, __shfl_xor(mt, 32));
+    float ps = 0.f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) ps += fast_exp2(sv[r] - mt);
+    ps += __shfl_xor(ps, 16);
+    ps += __shfl_xor(ps, 32);
+    if (g == 0) red[round & 1][w][col] = f32x2{mt, ps};
+    to_lds(Vs[w], vr);
+    load(Vp, t - W, vr);
+    __syncthreads();
+    // the tests of the round's tiles in order
+    f32x2 rd[W];
+#pragma unroll
+    for (int u = 0; u < W; ++u) rd[u] = red[round & 1][u][col];
+    bool mine = false;
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      const bool demand = (t0 - u >= t_lo) & head_valid &
+                          ((l == 0.f) | (rd[u][0] - (m + fast_log2(l)) >= thr2));
+      if (u == w) mine = demand;
+      if (demand) {
+        const float m_new = fmaxf(m, rd[u][0]);
+        l = l * fast_exp2(m - m_new) + rd[u][1] * fast_exp2(rd[u][0] - m_new);
+        m = m_new;
+        ++cnt;
+        if (p.counters) hsum += tile_hash(b, hq, 0, t0 - u);
+      }
+      if (p.counters) vloads += wave_any(demand) ? 1u : 0u;
+    }
+    if (wave_any(mine)) {
+      float alpha = 1.f;
+      if (mine) {
+        const float r_new = fmaxf(ref, mt);
+        alpha = fast_exp2(ref - r_new);
+        ref = r_new;
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) sv[r] = mine ? fast_exp2(sv[r] - ref) : 0.f;
+      bf16x8 ph, pl;
+      split_bf16x8(sv, ph, pl);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const bf16* vrow = Vs[w] + (4 * g + (col >> 2)) * LD + 16 * db + 4 * (col & 3);
+        const bf16x8 a = cat(lds_read_tr(vrow), lds_read_tr(vrow + 16 * LD));
+        acc[db] = mfma16(a, ph, acc[db] * alpha);
+        acc[db] = mfma16(a, pl, acc[db]);
+      }
+    }
+  }
+
+  // add the accumulators: through LDS (the V tiles' slots, 16 heads x D floats each), the
+  // first wavefront sums
+  if (w) {
+    float* out = reinterpret_cast<float*>(Vs[w]);
+    static_assert(sizeof(Vs[0]) >= 16 * D * sizeof(float), "an accumulator fits a V tile");
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+      *reinterpret_cast<f32x4*>(out + (db * 64 + lane) * 4) = acc[db];
+    if (g == 0) refs[w][col] = ref;
+  }
+  __syncthreads();
+  if (w == 0) {
+    // (a wavefront without retained tiles holds zeros and ref = -inf)
+    const float f0 = ref == kNegInf ? 1.f : fast_exp2(ref - m);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) acc[db] *= f0;
+#pragma unroll
+    for (int u = 1; u < W; ++u) {
+      const float r = refs[u][col], f = r == kNegInf ? 1.f : fast_exp2(r - m);
+      const float* in = reinterpret_cast<const float*>(Vs[u]);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        acc[db] += *reinterpret_cast<const f32x4*>(in + (db * 64 + lane) * 4) * f;
+    }
+    if (head_valid) write_split<D>(p, (long)b * p.Hq + hq, s, g, acc, m, l, cnt);
+    if (p.counters) {
+      const unsigned long long tiles = t_hi > t_lo ? t_hi - t_lo : 0;
+      if (head_valid && g == 0 && cnt) {
+        atomicAdd(&p.counters[kCntRetained], (unsigned long long)cnt);
+        atomicAdd(&p.counters[kCntSlots], (unsigned long long)cnt * kDecBk);
+        atomicAdd(&p.counters[kCntSetHash], hsum);
+      }
+      if (lane == 0 && tiles) {
+        atomicAdd(&p.counters[kCntLegal], tiles * nh);
+        atomicAdd(&p.counters[kCntVTiles], tiles);
+        atomicAdd(&p.counters[kCntVNeeded], (unsigned long long)vloads);
+      }
     }
   }
 }
@@ -313,24 +520,32 @@ __global__ __launch_bounds__(kCombineThreads) void mala_decode_combine_kernel(
   }
 }
 
-hipError_t launch_decode(const DecParams& p, int D, hipStream_t st) {
-  dim3 grid((unsigned)p.B * p.Hkv * p.nchunk * p.S), block(64);
-  if (D == 128)
-    hipLaunchKernelGGL(mala_decode_split_kernel<128>, grid, block, 0, st, p);
+// Up to one split per CU the chain of a split's tiles sets the time and a team takes it
+// (us per decode call with its merge, one wavefront / team of 4 / of 8 per split; D = 128):
+// 64 splits of 16 tiles 26.5 / 16.2 / 15.8, 256 of 16 27.9 / 19.6 / 20.9, 256 of 256 313 / 163
+// / 167, 64 of 782 881 / 378 / 327; D = 64, 128 of 64 65 / 31.8 / 26.7.  With 512 splits one
+// wavefront each does as well (28.9 / 28.8 / 36.5) and fetches only the V tiles it needs.
+template <int D>
+static void launch_decode_t(const DecParams& p, hipStream_t st) {
+  const unsigned n = (unsigned)p.B * p.Hkv * p.nchunk * p.S;
+  const int w = n > (unsigned)kNumCus || p.tps < 2 ? 1 : n <= 128 && p.tps >= 32 ? 8 : 4;
+  if (w == 8)
+    hipLaunchKernelGGL((mala_decode_team_kernel<D, 8>), dim3(n), dim3(512), 0, st, p);
+  else if (w == 4)
+    hipLaunchKernelGGL((mala_decode_team_kernel<D, 4>), dim3(n), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL(mala_decode_split_kernel<64>, grid, block, 0, st, p);
-  return hipGetLastError();
+    hipLaunchKernelGGL(mala_decode_split_kernel<D>, dim3(n), dim3(64), 0, st, p);
+  if (p.S > 1)
+    hipLaunchKernelGGL(mala_decode_combine_kernel<D>, dim3((unsigned)p.B * p.Hq),
+                       dim3(kCombineThreads), 0, st, p.part, p.o, (bool)p.o_bf16, p.lse,
+                       p.head_tiles, p.S);
 }
 
-hipError_t launch_decode_combine(const float* part, void* o, bool o_bf16, float* lse,
-                                 int32_t* head_tiles, int BH, int S, int D, hipStream_t st) {
-  dim3 grid((unsigned)BH), block(kCombineThreads);
+hipError_t launch_decode(const DecParams& p, int D, hipStream_t st) {
   if (D == 128)
-    hipLaunchKernelGGL(mala_decode_combine_kernel<128>, grid, block, 0, st, part, o, o_bf16,
-                       lse, head_tiles, S);
+    launch_decode_t<128>(p, st);
   else
-    hipLaunchKernelGGL(mala_decode_combine_kernel<64>, grid, block, 0, st, part, o, o_bf16,
-                       lse, head_tiles, S);
+    launch_decode_t<64>(p, st);
   return hipGetLastError();
 }
 

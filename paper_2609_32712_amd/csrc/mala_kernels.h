@@ -235,6 +235,10 @@ struct DecParams {
   const __bf16* k;
   const __bf16* v;
   float* part;         // [B, Hq, S, D + kDecStride]
+  void* o;             // [B, Hq, D] fp32, or bf16 when o_bf16; lse, head_tiles: [B, Hq]
+  int o_bf16;          // (written by the split kernels when S == 1, else by the merge)
+  float* lse;
+  int32_t* head_tiles; // or null
   unsigned long long* counters;
   const int32_t* lens; // [B] valid cache tokens per sequence, or null (all Nk)
   int B, Hq, Hkv, Nk, S, T, tps;   // T, tps: tiles and tiles per split at length Nk
@@ -249,7 +253,5 @@ hipError_t launch_bwd_preprocess(const void* o, bool o_bf16, const __bf16* dout,
                                  long rows, int D, hipStream_t st);
 hipError_t launch_bwd(const BwdParams& p, int D, hipStream_t st);
 hipError_t launch_decode(const DecParams& p, int D, hipStream_t st);
-hipError_t launch_decode_combine(const float* part, void* o, bool o_bf16, float* lse,
-                                 int32_t* head_tiles, int BH, int S, int D, hipStream_t st);
 
 }  // namespace mala

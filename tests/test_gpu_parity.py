@@ -558,6 +558,30 @@ def test_decode_full_lengths_match_uniform_path():
             np.testing.assert_allclose(host(b["o"]), host(a["o"]), atol=1e-5)
 
 
+@pytest.mark.parametrize("Hq,Hkv,N,D,splits,tau", [
+    (8, 2, 33, 128, 1, 1e-3), (4, 1, 129, 64, 1, 0.0), (40, 2, 257, 128, 2, 1.0),
+    (8, 2, 2049, 64, 2, 1e-2), (8, 2, 8191, 128, 3, 1.0), (2, 1, 1000, 128, 40, 1e-4)])
+def test_decode_team_matches_one_wavefront_per_split(Hq, Hkv, N, D, splits, tau):
+    # Up to 256 splits in a call run on teams of 4 or 8 wavefronts, more on one wavefront
+    # each: the same query and cache alone and in a batch of more than 256 splits.  The
+    # sums are taken in another order (fp32, a few hundred terms: 1e-5 relative to the
+    # O rows' size, ~1).
+    B = 256 // (Hkv * splits) + 1
+    w = Workload(dict(kind="decode", B=1, Hq=Hq, Hkv=Hkv, N=N, D=D, beta=3.0, needles=2))
+    t = w.tensors()
+    one = [dev(t[x]) for x in ("q", "k", "v")]
+    many = [x.expand(B, *x.shape[1:]).contiguous() for x in one]
+    a, b = (mala.decode(*x, f32(w.scale), tau, splits) for x in (one, many))
+    torch.cuda.synchronize()
+    for i in (0, B - 1):
+        assert torch.equal(a["head_tiles"][0], b["head_tiles"][i])
+        np.testing.assert_allclose(host(b["o"][i]), host(a["o"][0]), atol=1e-5)
+        np.testing.assert_allclose(host(b["lse"][i]), host(a["lse"][0]), atol=1e-5)
+    ca, cb = counters(a["counters"]), counters(b["counters"])
+    for i in (mala.CNT_LEGAL, mala.CNT_RETAINED, mala.CNT_SLOTS, mala.CNT_V_NEEDED):
+        assert cb[i] == B * ca[i], i
+
+
 def test_decode_splits_cover_dense_at_tau0():
     spec = dict(kind="decode", B=1, Hq=4, Hkv=1, N=2048, D=128, beta=3.0, needles=4)
     w = Workload(spec)
