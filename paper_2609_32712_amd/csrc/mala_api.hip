@@ -181,15 +181,14 @@ int run_bwd(const void* q, const void* k, const void* v, const Packed& pk,
   if (counters && (e = mala::launch_fill_zero(counters, mala::kNumCounters * sizeof(int64_t), s)) != hipSuccess)
     return hip_fail(e, "mala_bwd: clearing counters");
   float* dvec = (float*)workspace;
-  if ((e = mala::launch_bwd_preprocess(o, o_dtype == MALA_OUT_BF16, (const __bf16*)dout, dvec,
-                                       rows, D, s)) != hipSuccess)
-    return hip_fail(e, "mala_bwd: preprocess launch");
   mala::BwdParams p;
   p.q = (const __bf16*)q;
   p.k = (const __bf16*)k;
   p.v = (const __bf16*)v;
   p.dout = (const __bf16*)dout;
   p.lse = lse;
+  p.o = o;
+  p.o_bf16 = o_dtype == MALA_OUT_BF16;
   p.dvec = dvec;
   p.dq = dq; p.dk = dk; p.dv = dv;
   p.grad_bf16 = grad_dtype == MALA_OUT_BF16;

@@ -15,6 +15,9 @@
 //                         s - lse_q >= log2(tau) - log2(L_q) (base-2 units); ballot
 //   retained path         P = exp2(S - lse); dP^T = V dO^T; dS = P (dP - D_q);
 //                         dQ^T += K^T dS^T
+// Calls of few query rows run mala_bwd_dq_rows_kernel instead, 32 rows per workgroup, the
+// same bits; it also forms D_q = rowsum(O * dO), for which the others have a kernel of
+// their own.
 // mala_bwd_dkdv_kernel (key-major, Algorithm 2's traversal): one workgroup owns 128
 // keys of one (batch, KV head) and keeps their dK and dV in registers (no atomics,
 // bitwise reproducible); it sweeps the query tiles of every query head of the GQA
@@ -85,27 +88,53 @@ __global__ __launch_bounds__(256) void mala_bwd_preprocess_kernel(const OT* o, c
   if (row < rows && part == 0) dvec[row] = s;
 }
 
-template <typename OT>
-static void launch_preprocess_t(const OT* o, const bf16* dout, float* dvec, long rows, int D,
-                                hipStream_t st) {
-  const unsigned grid = (unsigned)((rows + 15) / 16);
-  if (D == 128)
-    hipLaunchKernelGGL((mala_bwd_preprocess_kernel<128, OT>), dim3(grid), dim3(256), 0, st, o,
-                       dout, dvec, rows);
-  else
-    hipLaunchKernelGGL((mala_bwd_preprocess_kernel<64, OT>), dim3(grid), dim3(256), 0, st, o,
-                       dout, dvec, rows);
+template <int D, typename OT>
+static void launch_preprocess(const OT* o, const BwdParams& p, long rows, hipStream_t st) {
+  hipLaunchKernelGGL((mala_bwd_preprocess_kernel<D, OT>), dim3((unsigned)((rows + 15) / 16)),
+                     dim3(256), 0, st, o, p.dout, p.dvec, rows);
 }
 
-hipError_t launch_bwd_preprocess(const void* o, bool o_bf16, const bf16* dout, float* dvec,
-                                 long rows, int D, hipStream_t st) {
-  if (o_bf16)
-    launch_preprocess_t(static_cast<const bf16*>(o), dout, dvec, rows, D, st);
-  else
-    launch_preprocess_t(static_cast<const float*>(o), dout, dvec, rows, D, st);
-  return hipGetLastError();
+// The same D_q, bit for bit, for the query row (row index row of the q-shaped tensors) whose
+// dO a lane of the transposed products holds as the operand ob: the sums of the kernel
+// above's 16 parts of D / 16 columns, two halves of which lie in the lane pair (h), added
+// in its order (parts 8, 4, 2, 1 apart).
+template <int D>
+__device__ __forceinline__ float row_dot(const BwdParams& p, long row, int h, bool valid,
+                                         const bf16x8 (&ob)[D / 16]) {
+  constexpr int KS = D / 16, PER = D / 16, NP = 8 / PER;   // parts per lane and k-step
+  float a[KS][NP];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const long i = row * D + 16 * kk + 8 * h;
+    if (valid) {
+      if (p.o_bf16) {
+        const bf16x8 v = load8(static_cast<const bf16*>(p.o) + i);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (float)v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = static_cast<const float*>(p.o)[i + e];
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) s += o[PER * x + e] * (float)ob[kk][PER * x + e];
+      a[kk][x] = s;
+    }
+  }
+#pragma unroll
+  for (int w = KS / 2; w >= 1; w >>= 1)
+#pragma unroll
+    for (int kk = 0; kk < w; ++kk)
+#pragma unroll
+      for (int x = 0; x < NP; ++x) a[kk][x] += a[kk + w][x];
+  float s = halves_sum(a[0][0]);
+  if (NP == 2) s += halves_sum(a[0][NP - 1]);
+  return s;
 }
-
 
 // S = Q K^T for one 32 x 32 tile: A = Q rows (lane row q, 8 of d), B = K rows
 // (lane column key, 8 of d); the k-steps accumulate in order in one chain.  Both
@@ -173,19 +202,17 @@ __device__ __forceinline__ void probabilities(float (&sv)[16], float scale2, con
   }
 }
 
-// Per-row vectors of a query tile: base-2 lse, test threshold, D_q.
+// Per-row vectors of a query tile: base-2 lse, test threshold.
 __device__ __forceinline__ void row_vectors(const BwdParams& p, long qbase, int Nq, long qq,
-                                            long off, float* lse2, float* thr, float* dv) {
+                                            long off, float* lse2, float* thr) {
 #pragma clang fp contract(off)
   if (qq < Nq) {
     const float l2 = p.lse[qbase + qq] * kLog2e;
     *lse2 = l2;
     *thr = l2 + p.log2tau - log2f((float)(qq + 1 + off));
-    *dv = p.dvec[qbase + qq];
   } else {
     *lse2 = 0.f;
     *thr = __builtin_huge_valf();   // padded rows never retain
-    *dv = 0.f;
   }
 }
 
@@ -1067,8 +1094,9 @@ __global__ __launch_bounds__(kDqWaves * 64) void mala_bwd_dq_kernel(BwdParams p)
     ob[kk] = row_valid ? load8(p.dout + off_e) : zero8();
   }
   // this lane's row vectors: base-2 lse, test threshold, D_q
-  float lse2, thr, dvq;
-  row_vectors(p, qbase, Nq, (long)qrow, off, &lse2, &thr, &dvq);
+  float lse2, thr;
+  row_vectors(p, qbase, Nq, (long)qrow, off, &lse2, &thr);
+  const float dvq = row_valid ? p.dvec[qbase + qrow] : 0.f;
   f32x16 negd;
 #pragma unroll
   for (int r = 0; r < 16; ++r) negd[r] = -dvq;
@@ -1261,6 +1289,253 @@ __global__ __launch_bounds__(kDqWaves * 64) void mala_bwd_dq_kernel(BwdParams p)
   }
 }
 
+// dQ pass of small grids: one workgroup of eight wavefronts per 32 query rows, four key
+// tiles (one block of 128 keys) at a time, for the same reason as the forward's kernel of
+// few row blocks: a call with few rows takes as long as one row block's chain of tiles
+// (~1.3 us each above), most of which need not be serial.  The sums and decisions keep
+// their order: the same bits.  Per stage of four tiles, from the last one down:
+//   * producers (wavefronts 0-3, one tile each), step n: S, the offline test, P, dP and dS,
+//     handed on through LDS as bf16 operands (hi and lo) with the rows' sums of |dS|;
+//   * consumers (wavefronts 4-7), step n + 1: the lo-term budget in tile order, then columns
+//     32 w .. 32 w + 31 of dQ over the retained tiles in order; the first one also records
+//     the decisions.
+// One head of 1024 tokens (D = 64): backward 60 -> 34 us, 2 x 4 heads x 700 69 -> 45 us, with
+// D_q formed here from O and the dO operands instead of a kernel before (~5 us).
+// K stages rotate through three LDS slots (loading, producers, consumers), a V tile goes to
+// its producer's own slot, both a stage ahead.  The hand-off has one buffer (LDS is full at
+// D = 128): a barrier in the middle of a step separates its readers from its writers.
+template <int D>
+__global__ __launch_bounds__(512) void mala_bwd_dq_rows_kernel(BwdParams p) {
+  constexpr int KS = D / 16, DB = D / 32, W = kBwdKeys / kBk;
+  constexpr int STAGE = tile_elems<D>(kBwdKeys);
+  constexpr int NIS = STAGE / 512;                       // 64-position loads per K stage
+  static_assert(NIS * 512 == STAGE, "whole loads per stage");
+  constexpr int NJS = (NIS + W - 1) / W;
+  constexpr int NVL = (tile_elems<D>(kBk) + 511) / 512;  // 64-position loads per V tile
+  __shared__ __attribute__((aligned(16))) bf16 Ks[3][STAGE];
+  __shared__ __attribute__((aligned(16))) bf16 Vs[W][NVL * 512];
+  __shared__ __attribute__((aligned(16))) bf16x8 hand[W][4][64];   // dS of a tile: hi0, hi1, lo0, lo1
+  __shared__ float asum[W][kBq];                         // per row: sum of |dS| of a tile
+  __shared__ int retained[W];
+  __shared__ unsigned long long bcnt[kNumCounters];      // the workgroup's counter sums
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5, c = lane & 31, G = lane >> 4, t16 = lane & 15;
+  const int BH = p.B * p.Hq;
+  const int bh = blockIdx.x % BH;
+  const int qt = (int)(gridDim.x / BH) - 1 - (int)(blockIdx.x / BH);   // longest rows first
+  const int b = bh / p.Hq, hq = bh % p.Hq, hkv = hq / (p.Hq / p.Hkv);
+  const Seg sg = seq_slice(p, b);
+  const int Nq = sg.Nq, Nk = sg.Nk;
+  const int q0w = qt * kBq;
+  if (q0w >= Nq) return;   // past the end of a packed sequence
+  const int offi = Nk - Nq;
+  const int qrow = q0w + c;
+  const bool row_valid = qrow < Nq;
+  const long qbase = sg.qb + (long)hq * p.Nq;    // row 0 of this (sequence, head)
+  const long kbase = sg.kb + (long)hkv * p.Nk;
+  if (p.counters) blk_init(bcnt);
+  const int jdiag = (min(q0w + kBq, Nq) - 1 + offi) / kBk;
+  const int ttop = jdiag / W, T = ttop + 1;      // stage n is the block of keys ttop - n
+  // slot u of stage n is key tile W (ttop - n) + W - 1 - u
+
+  if (wave < W) {
+    const bf16* Kp = p.k + kbase * D;
+    const bf16* Vp = p.v + kbase * D;
+    uint32_t k_off[NJS], v_off[NVL];
+#pragma unroll
+    for (int u = 0; u < NJS; ++u) k_off[u] = dma_lane_offset<D>(64 * (wave + W * u) + lane);
+#pragma unroll
+    for (int u = 0; u < NVL; ++u) v_off[u] = dma_lane_offset<D>(64 * u + lane);
+    auto fetch_k = [&](int n) {
+      const long k0 = (long)(ttop - n) * kBwdKeys;
+      const i32x4 rk = rsrc_words(Kp + k0 * D, (uint32_t)(Nk - k0) * (uint32_t)D * 2u);
+#pragma unroll
+      for (int u = 0; u < NJS; ++u) {
+        const int j = wave + W * u;
+        if (j < NIS) buf_load_lds16(rk, k_off[u], &Ks[n % 3][512 * j]);
+      }
+    };
+    auto fetch_v = [&](int j) {   // tiles above the diagonal read as zeros
+      const long k0 = (long)max(j, 0) * kBk;
+      const i32x4 rv = rsrc_words(Vp + k0 * D, j >= 0 && j <= jdiag
+                                                   ? (uint32_t)(Nk - k0) * (uint32_t)D * 2u : 0u);
+#pragma unroll
+      for (int u = 0; u < NVL; ++u) buf_load_lds16(rv, v_off[u], &Vs[wave][512 * u]);
+    };
+    fetch_k(0);
+    fetch_v(W * ttop + W - 1 - wave);
+    // Q and dO rows as B operands (lane column qrow), and the row's vectors
+    bf16x8 qb[KS], ob[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      const long i = (qbase + qrow) * D + 16 * kk + 8 * h;
+      qb[kk] = row_valid ? load8(p.q + i) : zero8();
+      ob[kk] = row_valid ? load8(p.dout + i) : zero8();
+    }
+    float lse2, thr;
+    row_vectors(p, qbase, Nq, (long)qrow, (long)offi, &lse2, &thr);
+    const float dvq = row_dot<D>(p, qbase + qrow, h, row_valid, ob);
+    if (wave == 0 && row_valid && h == 0) p.dvec[qbase + qrow] = dvq;
+    const int rdo = rd_base<D>(c, h);
+    const bf16* vr = lds_pin(&Vs[wave][rdo]);
+    wait_vm();
+    __syncthreads();
+
+    for (int n = 0; n <= T; ++n) {
+      bool ret = false;
+      float as_row = 0.f;
+      bf16x8 dh[2], dl[2];
+      const int j = W * (ttop - n) + W - 1 - wave;
+      if (n + 1 < T) fetch_k(n + 1);
+      bf16x8 vop[KS];
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) vop[kk] = load8(vr + rd_step<D>(kk));
+      // the slot is free once its reads have arrived: the next stage's tile takes it
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(vop[kk])::"memory");
+      if (n + 1 < T) fetch_v(j - W);
+      if (n < T && j <= jdiag) {
+        const int kb = j * kBk;
+        const bf16* kr = lds_pin(&Ks[n % 3][rdo + (W - 1 - wave) * kBk * (D + 8)]);
+        bf16x8 kop[KS];
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) kop[kk] = load8(kr + rd_step<D>(kk));
+        const f32x16 s = qk_tile<KS>(kop, qb);
+        const bool need_mask = (kb + kBk - 1 > q0w + offi) || (q0w + kBq > Nq) || (kb + kBk > Nk);
+        const int kmax = qrow + offi - kb - 4 * h;
+        const int klim = min(Nk - kb, kBk) - 4 * h;
+        float sv[16];
+        const bool dem = need_mask ? offline_test_t<true>(s, p.scale2, kmax, klim, thr, sv)
+                                   : offline_test_t<false>(s, p.scale2, kmax, klim, thr, sv);
+        ret = wave_any(dem);
+        if (ret) {
+          f32x16 dpd;   // dP^T - D: the accumulator starts at -D_q (one row per lane)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dpd[r] = -dvq;
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) dpd = mfma32(vop[kk], ob[kk], dpd);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sv[r] = fast_exp2(__builtin_fmaf(sv[r], p.scale2, -lse2));
+          float dsv[16], as = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dsv[r] = sv[r] * dpd[r];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) as += fabsf(dsv[r]);
+          as_row = halves_sum(as);
+          dh[0] = hi_bf16x8(dsv);
+          dh[1] = hi_bf16x8(dsv + 8);
+          dl[0] = lo_bf16x8(dsv, dh[0]);
+          dl[1] = lo_bf16x8(dsv + 8, dh[1]);
+        }
+      }
+      __syncthreads();             // the consumers are done with the last stage's dS
+      if (ret) {
+        hand[wave][0][lane] = dh[0];
+        hand[wave][1][lane] = dh[1];
+        hand[wave][2][lane] = dl[0];
+        hand[wave][3][lane] = dl[1];
+        if (h == 0) asum[wave][c] = as_row;
+      }
+      if (lane == 0) retained[wave] = ret ? 1 : 0;
+      wait_vm();                   // this wavefront's part of the next stage
+      __syncthreads();
+    }
+  } else {
+    const int cw = wave - W;
+    const int tro = tr_base<D>(4 * h + (t16 >> 2), G & 1, t16);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    float fdq = 0.f;   // this row's sum of |dS| in tiles run without the lo term
+    int cnt_row = 0;   // retained tiles in which row qrow has a legal key
+    unsigned n_ret = 0;
+    unsigned long long hsum = 0;   // fingerprints of the retained tiles
+    // the decisions for the key-major pass, one byte per block: lane i % 64 holds block i's
+    // until the 64 of a group go out together
+    uint8_t* mrow = p.mask + mask_index(p, mask_row0(p, b, sg) + qt, hq, 0);
+    uint32_t pack = 0;
+    __syncthreads();
+    for (int n = 0; n <= T; ++n) {
+      if (n > 0) {
+        const int blk = ttop - (n - 1);
+        int keep = 0, nib = 0;
+#pragma unroll
+        for (int u = 0; u < W; ++u) {
+          const int r = __builtin_amdgcn_readfirstlane(retained[u]);
+          keep |= r << u;
+          nib |= r << (W - 1 - u);
+        }
+        if (cw == 0) {
+          if (lane == (blk & 63)) pack = (uint32_t)nib;
+          if (!(blk & 63) && lane <= ttop - blk) mrow[blk + lane] = (uint8_t)pack;
+          n_ret += __popc(keep);
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+            if ((keep >> u) & 1) {
+              const int j = W * blk + W - 1 - u;
+              cnt_row += row_valid && j * kBk <= qrow + offi ? 1 : 0;
+              if (p.counters) hsum += tile_hash(b, hq, qt, j);
+            }
+        }
+        if (keep && cw < DB) {
+          float as[W];
+          bf16x8 ko[W][2], dh[W][2];
+          const bf16* ktb = lds_pin(&Ks[(n - 1) % 3][tro + tr_step<D>(0) + 8 * cw]);
+#pragma unroll
+          for (int u = 0; u < W; ++u) {
+            as[u] = asum[u][c];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+              const bf16* kt = ktb + ((W - 1 - u) * kBk + 16 * ks) * (D + 8);
+              ko[u][ks] = cat(lds_read_tr(kt), lds_read_tr(kt + 8 * (D + 8)));
+              dh[u][ks] = hand[u][ks][lane];
+            }
+          }
+          // dQ^T[d][q] += K^T[d][key] dS^T[key][q]; without dS's lo term while this row's
+          // sum of |dS| over such tiles stays within kLoMassDq (for every row of the block);
+          // a tile holding more than kLoTileDq of some row's |dS| always takes it
+#pragma unroll
+          for (int u = 0; u < W; ++u) {
+            if (!((keep >> u) & 1)) continue;
+            const float fq_new = fdq + as[u];
+            const bool with_lo = wave_any(fq_new > kLoMassDq || as[u] > kLoTileDq);
+            if (!with_lo) fdq = fq_new;
+            acc = mfma32(ko[u][0], dh[u][0], acc);
+            acc = mfma32(ko[u][1], dh[u][1], acc);
+            if (with_lo) {
+              acc = mfma32(ko[u][0], hand[u][2][lane], acc);
+              acc = mfma32(ko[u][1], hand[u][3][lane], acc);
+            }
+          }
+        }
+      }
+      __syncthreads();
+      __syncthreads();
+    }
+    // dQ = scale * sum dS K; lane (h, c) holds row qrow, columns 32 cw + 8 g + 4 h + e
+    if (row_valid) {
+      if (cw < DB) {
+        const long qr = (qbase + qrow) * D + 32 * cw + 4 * h;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          store_out4(p.dq, qr + 8 * g,
+                     f32x4{acc[4 * g] * p.scale, acc[4 * g + 1] * p.scale, acc[4 * g + 2] * p.scale,
+                           acc[4 * g + 3] * p.scale}, p.grad_bf16);
+      }
+      if (cw == 0 && h == 0 && p.row_tiles) p.row_tiles[qbase + qrow] = cnt_row;
+    }
+    if (p.counters && cw == 0 && lane == 0) {
+      blk_add(bcnt, kCntLegal, jdiag + 1);
+      blk_add(bcnt, kCntRetained, n_ret);
+      blk_add(bcnt, kCntSlots, (unsigned long long)n_ret * kBk * min(kBq, Nq - q0w));
+      blk_add(bcnt, kCntSetHash, hsum);
+    }
+  }
+  if (p.counters) blk_flush(bcnt, p.counters);
+}
+
 // Sum of the parts of split dK/dV sweeps in part order (fixed-length batches): one
 // thread per four columns of a K-shaped row; a row's key block has
 // ceil(iterations / psize) parts.
@@ -1296,6 +1571,7 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
 // promise.  Both kernels are then launched and one of them leaves at once, at ~1.2 us per
 // workgroup: under 2% of sweeps of 512 iterations and more.  8 x 4096 language-model-like
 // tokens at tau = 1: 872 / 522.
+constexpr float kSparseLog2Tau = -3.33f;   // log2 of 0.1: tolerances that may skip many tiles
 enum class DkdvRule { kPairs, kBlocks, kBySequence };
 static DkdvRule dkdv_rule(const BwdParams& p) {
   long n = (long)p.nkblk * p.B * p.Hkv;
@@ -1303,7 +1579,7 @@ static DkdvRule dkdv_rule(const BwdParams& p) {
   n *= p.nparts;
   if (n <= kNumCus) return DkdvRule::kPairs;
   const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
-  return p.log2tau >= -3.33f && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
+  return p.log2tau >= kSparseLog2Tau && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
 }
 
 template <int D>
@@ -1313,7 +1589,22 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
   const DkdvRule rule = dkdv_rule(p);
   p.by_sequence = rule == DkdvRule::kBySequence;
   // the dQ pass first: it records the tile decisions that the key-major pass follows
-  hipLaunchKernelGGL(mala_bwd_dq_kernel<D>, grid_q, block_q, 0, st, p);
+  // (dQ pass, us per backward, other kernel / rows kernel, D = 128 GQA 8/2 unless stated: 128
+  // tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,
+  // 32 heads 2048 238 / 298.  At tau = 1, where the other kernel skips for less, 2048
+  // language-model-like tokens 177 / 157, 4096 331 / 339)
+  if (few_row_blocks(p, p.log2tau >= kSparseLog2Tau ? 2 : 3)) {
+    hipLaunchKernelGGL(mala_bwd_dq_rows_kernel<D>, dim3((unsigned)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq), dim3(512),
+                       0, st, p);
+  } else {
+    // D_q over every row of the q-shaped tensors (packed: all heads x total rows)
+    const long rows = (p.cu ? 1l : p.B) * p.Hq * p.Nq;
+    if (p.o_bf16)
+      launch_preprocess<D>(static_cast<const bf16*>(p.o), p, rows, st);
+    else
+      launch_preprocess<D>(static_cast<const float*>(p.o), p, rows, st);
+    hipLaunchKernelGGL(mala_bwd_dq_kernel<D>, grid_q, block_q, 0, st, p);
+  }
   if (rule != DkdvRule::kPairs)
     hipLaunchKernelGGL(mala_bwd_dkdv_kernel<D>, dim3(n), dim3(1024), 0, st, p);
   if (rule != DkdvRule::kBlocks)

@@ -232,6 +232,7 @@ __device__ __forceinline__ void store_out4(void* base, long i, f32x4 v, bool to_
 // The post-score products (P V, P^T dO, dS^T Q, dS K) run as two MFMAs, one per
 // term, so the probabilities keep ~16 significant bits instead of bf16's 8.
 __device__ __forceinline__ void split_bf16x8(const float* x, bf16x8& hi, bf16x8& lo) {
+#pragma clang fp contract(off)   // x - hi of x as rounded, also where x is a product
   // one packed conversion per pair; the high parts come back to fp32 by bit moves
   // (a bf16 is the upper half of an fp32), so x - hi is exact
 #pragma unroll
@@ -261,6 +262,7 @@ __device__ __forceinline__ bf16x8 hi_bf16x8(const float* x) {
 
 // The low bf16 terms of x given its high terms hi (as hi_bf16x8 returned them).
 __device__ __forceinline__ bf16x8 lo_bf16x8(const float* x, bf16x8 hi) {
+#pragma clang fp contract(off)   // x - hi of x as rounded, also where x is a product
   bf16x8 lo;
 #pragma unroll
   for (int i = 0; i < 8; i += 2) {

@@ -23,8 +23,6 @@
 //                         row's normalizer, O^T += V^T P^T (8 MFMAs per term, V^T
 //                         operand through ds_read_b64_tr_b16).
 // A skipped tile costs its QK MFMAs, one max reduction and one compare.
-#include <algorithm>
-
 #include "mala_device.h"
 #include "mala_kernels.h"
 
@@ -345,7 +343,6 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
 // 8 heads against 16384 keys: 465 -> 145 us; one head over 1024 rows (D = 128): 43 -> 16
 // us.  K straight into operand registers instead of LDS took 1600 cycles of issue per
 // step (32-byte pieces of a row per load), a fetch of V by the consumers 1300.
-constexpr int kRowsTiles = 4;                     // key tiles per stage
 template <int D>
 __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdParams p) {
   constexpr int W = kRowsTiles, KS = D / 16, DB = D / 32;
@@ -661,25 +658,15 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
   }
 }
 
-// Whether a call takes the rows kernel: where its time is the chain of one row block's
-// tiles and not the chip's throughput.  In units of one step of that kernel (1.1 us) its
-// row blocks take the mean of (stages + 3) each over 256 CUs; the chain of the other
-// kernel takes 3.3 such units per stage of the longest block.  Measured (D = 128, us,
-// other kernel / rows kernel; 32 query heads unless stated): 256 x 256 17.8 / 10.7,
-// 512 x 512 28.1 / 20.5, 1024 x 1024 47.8 / 49.3, 2048 x 2048 85 / 129; 8 heads 2048 x
-// 2048 76.8 / 37.4, 4096 x 4096 136 / 106, 512 x 8192 245 / 81, 2048 x 8192 246 / 149; one
-// stage (64 x 64) 6.4 / 8.6, which stays with the other kernel.  Packed batches hold at
-// most total / 32 + sequences row blocks, taken as long as the longest.  The counters of
-// V tiles are defined by groups of 256 rows, so calls with counters stay there too.
+// Whether a call takes the rows kernel.  Its chain of four tiles is ~3.3 of the rows
+// kernel's steps.  Measured (D = 128, us, other kernel / rows kernel; 32 query heads unless
+// stated): 256 x 256 17.8 / 10.7, 512 x 512 28.1 / 20.5, 1024 x 1024 47.8 / 49.3, 2048 x 2048
+// 85 / 129; 8 heads 2048 x 2048 76.8 / 37.4, 4096 x 4096 136 / 106, 512 x 8192 245 / 81, 2048 x
+// 8192 246 / 149; one stage (64 x 64) 6.4 / 8.6, which stays with the other kernel.  The
+// counters of V tiles are defined by groups of 256 rows, so calls with counters stay there
+// too.
 static bool use_rows_kernel(const FwdParams& p) {
-  const long max_stages = (p.max_len_k + kRowsTiles * kBk - 1) / (kRowsTiles * kBk);
-  const long grid = (long)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq;
-  const long blocks = p.cu ? std::min(grid, (long)p.Hq * (p.Nq / kBq + p.B)) : grid;
-  if (p.counters || max_stages < 2 || grid > 16 * kNumCus) return false;
-  if (blocks <= kNumCus) return true;
-  const long first = (p.max_len_k - p.max_len) / (kRowsTiles * kBk) + 1;   // shortest block's stages
-  const long stages2 = p.cu ? 2 * max_stages : first + max_stages;         // twice the mean
-  return blocks * (stages2 + 6) <= 2 * 3 * (long)kNumCus * max_stages;
+  return !p.counters && p.max_len_k > kRowsTiles * kBk && few_row_blocks(p, 3);
 }
 
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t st) {

@@ -114,6 +114,27 @@ __device__ __forceinline__ Seg seq_slice(const P& p, int b) {
   return Seg{p.Nq, p.Nk, (long)b * p.Hq * p.Nq, (long)b * p.Hkv * p.Nk};
 }
 
+// Whether a call's time is the chain of one row block's key tiles and not the chip's
+// throughput, so that the kernels of one workgroup per 32 query rows (the forward's and
+// the dQ pass's) are ahead of those of 256 rows.  In units of one step of the former (four
+// key tiles, ~1.1 us) its row blocks take the mean of (stages + 3) each over the CUs; the
+// chain of the latter takes `chain` such units per stage of the longest block.  Packed
+// batches hold at most total / 32 + sequences row blocks, taken as long as the longest.
+constexpr int kRowsTiles = 4;   // key tiles per stage of those kernels
+template <class P>
+inline bool few_row_blocks(const P& p, int chain) {
+  const long stage = kRowsTiles * kBk;
+  const long longest = (p.max_len_k + stage - 1) / stage;
+  const long grid = (long)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq;
+  long blocks = grid;
+  if (p.cu && (long)p.Hq * (p.Nq / kBq + p.B) < grid) blocks = (long)p.Hq * (p.Nq / kBq + p.B);
+  if (grid > 16 * kNumCus) return false;
+  if (blocks <= kNumCus) return true;
+  const long shortest = (p.max_len_k - p.max_len) / stage + 1;
+  const long mean2 = p.cu ? 2 * longest : shortest + longest;   // twice the mean
+  return blocks * (mean2 + 6) <= 2l * chain * kNumCus * longest;
+}
+
 struct FwdParams {
   const __bf16* q;
   const __bf16* k;
@@ -138,7 +159,9 @@ struct BwdParams {
   const __bf16* v;
   const __bf16* dout;
   const float* lse;
-  const float* dvec;   // D_q = rowsum(O_q * dO_q)
+  const void* o;       // fp32, or bf16 when o_bf16
+  int o_bf16;
+  float* dvec;         // D_q = rowsum(O_q * dO_q), from the dQ pass for the dK/dV pass
   void* dq;            // fp32, or bf16 when grad_bf16 (dk, dv alike)
   void* dk;
   void* dv;
@@ -249,8 +272,6 @@ struct DecParams {
 
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t st);
-hipError_t launch_bwd_preprocess(const void* o, bool o_bf16, const __bf16* dout, float* dvec,
-                                 long rows, int D, hipStream_t st);
 hipError_t launch_bwd(const BwdParams& p, int D, hipStream_t st);
 hipError_t launch_decode(const DecParams& p, int D, hipStream_t st);
 
