@@ -202,21 +202,25 @@ __device__ __forceinline__ void probabilities(float (&sv)[16], float scale2, con
   }
 }
 
-// Per-row vectors of a query tile: base-2 lse, test threshold.
+// Per-row vectors of a query tile: base-2 lse, test threshold, D_q.
 __device__ __forceinline__ void row_vectors(const BwdParams& p, long qbase, int Nq, long qq,
-                                            long off, float* lse2, float* thr) {
+                                            long off, float* lse2, float* thr, float* dv) {
 #pragma clang fp contract(off)
   if (qq < Nq) {
     const float l2 = p.lse[qbase + qq] * kLog2e;
     *lse2 = l2;
     *thr = l2 + p.log2tau - log2f((float)(qq + 1 + off));
+    *dv = p.dvec[qbase + qq];
   } else {
     *lse2 = 0.f;
     *thr = __builtin_huge_valf();   // padded rows never retain
+    *dv = 0.f;
   }
 }
 
-template <int D>
+// BYSEQ: sequences that retain few tiles are left to the pairs kernel (without the check
+// the kernel is ~2% faster on short sweeps).
+template <int D, bool BYSEQ>
 __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   constexpr int KS = D / 16;       // k-steps over head_dim
   constexpr int DB = D / 32;       // 32-wide column blocks
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   const int it0 = part * p.psize, it1 = min(total, it0 + p.psize);
   if (it0 >= total) return;
   const float budget_share = 1.f / (float)((total + p.psize - 1) / p.psize);
-  if (p.by_sequence &&
+  if (BYSEQ &&
       sparse_sequence<1024>(p, nqt, off, mask_row0(p, b, sg), reinterpret_cast<longlong2*>(Qs)))
     return;
   if (p.counters) blk_init(bcnt);
@@ -515,16 +519,12 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
             }
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) dpd = mfma32(oa[kk], kv[kk], dpd);
-            float pv[16], dd[16], ds[16];
+            float ds[16];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               const f32x4 p4 = Pf[t & 1][grp_k][g][lane];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                pv[4 * g + e] = p4[e];
-                dd[4 * g + e] = dpd[4 * g + e];
-                ds[4 * g + e] = p4[e] * dpd[4 * g + e];
-              }
+              for (int e = 0; e < 4; ++e) ds[4 * g + e] = p4[e] * dpd[4 * g + e];
             }
             // dK runs this tile without dS's lo term while the key's sum of |dS| in
             // such tiles stays within kLoMassDk (for every key of the tile); a tile
@@ -536,10 +536,15 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
             const float fk_new = fdk + as_key;
             const bool with_lo = wave_any(fk_new > kLoMassDk * budget_share || as_key > kLoTileDk);
             if (!with_lo) fdk = fk_new;
-            const bf16x8 xh[2] = {hi_bf16x8(ds), hi_bf16x8(ds + 8)};
+            bf16x8 xh[2], xl[2];
             if (with_lo) {
-              dSop[t & 1][grp_k][2][lane] = lo_product_bf16x8(pv, dd, xh[0]);
-              dSop[t & 1][grp_k][3][lane] = lo_product_bf16x8(pv + 8, dd + 8, xh[1]);
+              split_bf16x8(ds, xh[0], xl[0]);
+              split_bf16x8(ds + 8, xh[1], xl[1]);
+              dSop[t & 1][grp_k][2][lane] = xl[0];
+              dSop[t & 1][grp_k][3][lane] = xl[1];
+            } else {
+              xh[0] = hi_bf16x8(ds);
+              xh[1] = hi_bf16x8(ds + 8);
             }
             dSop[t & 1][grp_k][0][lane] = xh[0];
             dSop[t & 1][grp_k][1][lane] = xh[1];
@@ -852,7 +857,7 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
 #pragma unroll
           for (int kk = 0; kk < KS; ++kk) dpd = mfma32(oa[kk], vop[kk], dpd);
           probabilities(sv, p.scale2, rv, h);
-          float ps = 0.f, as = 0.f, ds[16], dd[16];
+          float ps = 0.f, as = 0.f, ds[16];
 #pragma unroll
           for (int r = 0; r < 16; ++r) ps += sv[r];
           bf16x8 (&hd)[8][64] = hand[s & 1][wave];
@@ -862,17 +867,14 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
           hd[2][lane] = lo_bf16x8(sv, p0);
           hd[3][lane] = lo_bf16x8(sv + 8, p1);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            dd[r] = dpd[r];
-            ds[r] = sv[r] * dpd[r];
-          }
+          for (int r = 0; r < 16; ++r) ds[r] = sv[r] * dpd[r];
 #pragma unroll
           for (int r = 0; r < 16; ++r) as += fabsf(ds[r]);
           const bf16x8 d0 = hi_bf16x8(ds), d1 = hi_bf16x8(ds + 8);
           hd[4][lane] = d0;
           hd[5][lane] = d1;
-          hd[6][lane] = lo_product_bf16x8(sv, dd, d0);
-          hd[7][lane] = lo_product_bf16x8(sv + 8, dd + 8, d1);
+          hd[6][lane] = lo_bf16x8(ds, d0);
+          hd[7][lane] = lo_bf16x8(ds + 8, d1);
           const float pk = halves_sum(ps), ak = halves_sum(as);
           if (h == 0) sums[s & 1][wave][c] = f32x2{pk, ak};
         }
@@ -1094,9 +1096,8 @@ __global__ __launch_bounds__(kDqWaves * 64) void mala_bwd_dq_kernel(BwdParams p)
     ob[kk] = row_valid ? load8(p.dout + off_e) : zero8();
   }
   // this lane's row vectors: base-2 lse, test threshold, D_q
-  float lse2, thr;
-  row_vectors(p, qbase, Nq, (long)qrow, off, &lse2, &thr);
-  const float dvq = row_valid ? p.dvec[qbase + qrow] : 0.f;
+  float lse2, thr, dvq;
+  row_vectors(p, qbase, Nq, (long)qrow, off, &lse2, &thr, &dvq);
   f32x16 negd;
 #pragma unroll
   for (int r = 0; r < 16; ++r) negd[r] = -dvq;
@@ -1374,8 +1375,13 @@ __global__ __launch_bounds__(512) void mala_bwd_dq_rows_kernel(BwdParams p) {
       qb[kk] = row_valid ? load8(p.q + i) : zero8();
       ob[kk] = row_valid ? load8(p.dout + i) : zero8();
     }
-    float lse2, thr;
-    row_vectors(p, qbase, Nq, (long)qrow, (long)offi, &lse2, &thr);
+    float lse2 = 0.f, thr = __builtin_huge_valf();   // padded rows never retain
+    if (row_valid) {
+      // the arithmetic of row_vectors
+#pragma clang fp contract(off)
+      lse2 = p.lse[qbase + qrow] * kLog2e;
+      thr = lse2 + p.log2tau - log2f((float)((long)qrow + 1 + offi));
+    }
     const float dvq = row_dot<D>(p, qbase + qrow, h, row_valid, ob);
     if (wave == 0 && row_valid && h == 0) p.dvec[qbase + qrow] = dvq;
     const int rdo = rd_base<D>(c, h);
@@ -1605,8 +1611,10 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
       launch_preprocess<D>(static_cast<const float*>(p.o), p, rows, st);
     hipLaunchKernelGGL(mala_bwd_dq_kernel<D>, grid_q, block_q, 0, st, p);
   }
-  if (rule != DkdvRule::kPairs)
-    hipLaunchKernelGGL(mala_bwd_dkdv_kernel<D>, dim3(n), dim3(1024), 0, st, p);
+  if (rule == DkdvRule::kBlocks)
+    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, false>), dim3(n), dim3(1024), 0, st, p);
+  if (rule == DkdvRule::kBySequence)
+    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n), dim3(1024), 0, st, p);
   if (rule != DkdvRule::kBlocks)
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_kernel<D>, dim3(4 * n), dim3(512), 0, st, p);
   if (p.nparts > 1) {

@@ -275,20 +275,4 @@ __device__ __forceinline__ bf16x8 lo_bf16x8(const float* x, bf16x8 hi) {
   return lo;
 }
 
-// The low bf16 terms of the products x[i] y[i] given their high terms hi, x y - hi with
-// one rounding: the backward's dS = P (dP - D).
-__device__ __forceinline__ bf16x8 lo_product_bf16x8(const float* x, const float* y, bf16x8 hi) {
-  bf16x8 lo;
-#pragma unroll
-  for (int i = 0; i < 8; i += 2) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, bf16x2{hi[i], hi[i + 1]});
-    const float h0 = __uint_as_float(u << 16), h1 = __uint_as_float(u & 0xffff0000u);
-    const bf16x2 l2 = __builtin_convertvector(
-        (f32x2{__builtin_fmaf(x[i], y[i], -h0), __builtin_fmaf(x[i + 1], y[i + 1], -h1)}), bf16x2);
-    lo[i] = l2[0];
-    lo[i + 1] = l2[1];
-  }
-  return lo;
-}
-
 }  // namespace mala

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
   int cnt = 0;          // retained diagonal tiles in which this row has a legal key
   unsigned n_ret_m = 0;  // retained diagonal tiles
-  const float thr = row_threshold(p.log2tau, qrow, off);   // log2(tau / L_q)
+  const float thr = p.log2tau - log2f((float)(qrow + 1 + off));   // log2(tau / L_q)
 
   const int qlast_w = min(q0w + kBq - 1, Nq - 1);
   const int jdiag = (q0w < Nq) ? (int)((qlast_w + off) / kBk) : -1;
@@ -206,24 +206,44 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
         const int kb = j * kBk;
         ++n_legal;
         // score discovery (all K operands are read from LDS first)
-        bf16x8 ka[KS];
+        f32x16 s;
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) ka[kk] = load8(kr + sub * kBk * (D + 8) + rd_step<D>(kk));
-        const f32x16 s = fwd_scores<KS>(ka, qreg);
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        {
+          bf16x8 ka[KS];
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) ka[kk] = load8(kr + sub * kBk * (D + 8) + rd_step<D>(kk));
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) s = mfma32(ka[kk], qreg[kk], s);
+        }
 
-        // keys of this lane: kb + 8 (r / 4) + 4 h + r % 4; legal iff key <= qrow + off
         const bool need_mask = (kb + kBk - 1 > q0w + offi) || (q0w + kBq > Nq);
         float sv[16];
+        float mt = kNegInf;
+        if (need_mask) {
+          // keys of this lane: kb + 8 (r / 4) + 4 h + r % 4; legal iff key <= qrow + off
+          const int lim = row_valid ? qrow + offi - kb - 4 * h : -1000000;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] : kNegInf;
+            sv[r] = x;
+            mt = fmaxf(mt, x);
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            sv[r] = s[r];
+            mt = fmaxf(mt, sv[r]);
+          }
+        }
         // the row max of the raw scores, then scaled (scale2 > 0 and rounding is
         // monotonic, so this is the max of the scaled scores)
-        const float raw = halves_max(masked_max(s, need_mask,
-                                                row_valid ? qrow + offi - kb - 4 * h : -1000000, sv));
-        const float mt = raw * p.scale2;
+        mt = halves_max(mt) * p.scale2;
 
         // the online test (rows with no legal key in the tile do not vote); m + log2(l)
         // is log2 of the retained normalizer whichever reference m the row uses
         const bool voter = row_valid & (kb <= qrow + offi);
-        const bool demand = voter & online_demand(raw, p.scale2, m, l, thr);
+        const bool demand = voter & ((l == 0.f) | (mt - m - fast_log2(l) >= thr));
         if (!wave_any(demand)) continue;    // skipped: m, l and O unchanged
         ++n_ret;
         // off the diagonal every valid row votes: those tiles are counted per wavefront
@@ -252,7 +272,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
         // rescaled.  The result is the same softmax; P stays in [0, 2^8].
         if (wave_any(mt > m + 8.f)) {
           const float m_new = fmaxf(m, mt);
-          const float alpha = rescale(m, m_new);
+          const float alpha = (m_new == kNegInf) ? 1.f : fast_exp2(m - m_new);
           l *= alpha;
           m = m_new;
 #pragma unroll
@@ -260,7 +280,15 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[db][r] *= alpha;
         }
-        const float ps = fwd_probabilities(sv, p.scale2, m);
+        // a row with no legal key so far keeps m = -inf: shift by 0 so exp2(-inf) = 0
+        const float shift = (m == kNegInf) ? 0.f : m;
+        // P = exp2(s scale2 - shift) with one rounding; the row sum as a tree
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sv[r] = fast_exp2(__builtin_fmaf(sv[r], p.scale2, -shift));
+        float ps4[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) ps4[g] = (sv[4 * g] + sv[4 * g + 1]) + (sv[4 * g + 2] + sv[4 * g + 3]);
+        const float ps = halves_sum((ps4[0] + ps4[1]) + (ps4[2] + ps4[3]));
         l += ps;
         // P as two bf16 terms where it matters: the backward's D = rowsum(O * dO)
         // cancels against dP for dominant keys, so their probabilities must be
