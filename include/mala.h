@@ -78,11 +78,12 @@ enum {
                             counted by the query-major dQ pass) */
   MALA_CNT_V_TILES = 2,  /* forward: V tiles of B_k keys staged (a workgroup of 256
                             query rows stages every key tile it visits);
-                            backward: dO tiles of B_q rows staged by the key-major pass
-                            (a workgroup of 128 keys stages only the query tiles that
-                            some of its key tiles retain);
+                            backward: dO tiles of B_q rows that the key-major pass
+                            needs per block of 128 keys (the query tiles that some of
+                            the block's key tiles retain);
                             decode: V tiles of B_k keys fetched (once per up to 16 query
-                            heads of a GQA group, look-ahead fetches included) */
+                            heads of a GQA group, look-ahead fetches included; calls of
+                            few splits fetch every tile) */
   MALA_CNT_SLOTS = 3,    /* post-score key slots summed over query rows: a retained
                             B_q x B_k tile adds B_k slots to each of its valid rows
                             (Attention Cost section; mean slots per query =
@@ -160,8 +161,13 @@ int mala_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
  * P = 4), which a last pass adds in part order.  0 for an invalid shape. */
 size_t mala_bwd_workspace_size(int B, int Hq, int Hkv, int Nq, int Nk, int D);
 
-/* Bytes of device workspace mala_bwd_varlen needs: Hq total_q floats of D_q and
- * Hq (total_q / B_q + num_seqs) ceil(max_seqlen_k / 128) decision bytes. */
+/* Bytes of device workspace mala_bwd_varlen works best with: Hq total_q floats of D_q and
+ * Hq (total_q / B_q + num_seqs) ceil(max_seqlen_k / 128) decision bytes, which it needs,
+ * and, where the batch has fewer than 1024 key blocks (Hkv (total_q / 128 + num_seqs)) and
+ * sweeps of more than 512 iterations, the fp32 dK and dV sums of the sweeps' parts as in
+ * mala_bwd (P x 2 x Hkv total_q D floats).  A call whose workspace has no room for the
+ * parts (P x 2 x Hkv total_k D floats) runs its sweeps whole: slower, and dK and dV then
+ * differ by their sums' rounding. */
 size_t mala_bwd_varlen_workspace_size(int num_seqs, int max_seqlen_k, int total_q, int Hq,
                                       int Hkv, int D);
 
@@ -223,8 +229,9 @@ int mala_fwd_varlen(const void* q, const void* k, const void* v, const int32_t* 
  * Packed variable-length batches: mala_bwd (Algorithm 2) per sequence, on the
  * layout of mala_fwd_varlen (o, lse as it returned them, o of type o_dtype; dout,
  * dq: [Hq, total_q, D]; dk, dv: [Hkv, total_k, D]; gradients of type grad_dtype).
- * workspace: at least mala_bwd_varlen_workspace_size(num_seqs, max_seqlen_k, total_q,
- * Hq, Hkv, D) bytes.  Rows that no sequence covers are not written.
+ * workspace: mala_bwd_varlen_workspace_size(num_seqs, max_seqlen_k, total_q, Hq, Hkv, D)
+ * bytes (or at least the part of them described there), 16-byte aligned.  Rows that no
+ * sequence covers are not written.
  */
 int mala_bwd_varlen(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_q,
                     const int32_t* cu_seqlens_k, const void* o, const float* lse,

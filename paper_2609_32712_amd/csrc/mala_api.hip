@@ -61,6 +61,27 @@ void dkdv_split(int B, int Hq, int Hkv, int Nq, int Nk, int* psize, int* nparts)
   *psize = (int)ps;
   *nparts = (int)((longest + ps - 1) / ps);
 }
+// Packed batches, whose lengths only the device knows: the same rule on what the host
+// knows, blocks of the total and sweeps up to the longest sequence's, half of it long on
+// average.  A sequence of at most psize iterations stays in one part.
+void dkdv_split_packed(int num_seqs, int max_q, int total_k, int Hq, int Hkv, int* psize,
+                       int* nparts) {
+  const long blocks = (long)Hkv * (total_k / mala::kBwdKeys + num_seqs);
+  const long longest = (long)(Hq / Hkv) * ((max_q + mala::kBq - 1) / mala::kBq);
+  *psize = 1 << 30;
+  *nparts = 1;
+  if (blocks >= mala::kDkdvSplitGroups) return;
+  long ps = mala::kDkdvPartMin;
+  while (ps * 4 * mala::kDkdvSplitGroups <= blocks * longest) ps *= 2;
+  if (ps >= longest) return;
+  *psize = (int)ps;
+  *nparts = (int)((longest + ps - 1) / ps);
+}
+size_t part_bytes_packed(int num_seqs, int max_q, int total_k, int Hq, int Hkv, int D) {
+  int psize, nparts;
+  dkdv_split_packed(num_seqs, max_q, total_k, Hq, Hkv, &psize, &nparts);
+  return nparts > 1 ? round_up((size_t)nparts * 2 * Hkv * total_k * D * sizeof(float), 256) : 0;
+}
 // fp32 partial dV and dK of every part of the split sweeps (fixed-length batches)
 size_t part_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D) {
   int psize, nparts;
@@ -173,7 +194,7 @@ int run_fwd(const void* q, const void* k, const void* v, const Packed& pk,
 int run_bwd(const void* q, const void* k, const void* v, const Packed& pk,
             const void* o, int o_dtype, const float* lse, const void* dout, void* dq, void* dk,
             void* dv, int grad_dtype, int32_t* row_tiles, int64_t* counters, void* workspace,
-            int B, int Hq, int Hkv, int Nq, int Nk, int D, float scale, float tau,
+            size_t workspace_bytes, int B, int Hq, int Hkv, int Nq, int Nk, int D, float scale, float tau,
             hipStream_t s) {
   hipError_t e;
   // D_q over every row of the q-shaped tensors (packed: all heads x total rows)
@@ -206,12 +227,18 @@ int run_bwd(const void* q, const void* k, const void* v, const Packed& pk,
   p.nqblk = (p.max_len + mala::kDqRows - 1) / mala::kDqRows;
   p.mask = (uint8_t*)workspace + dvec_bytes(rows);
   p.mask_rows = mask_rows(pk.cu != nullptr, B, Nq);
-  p.psize = 1 << 30;
-  p.nparts = 1;
-  p.part = nullptr;
+  const size_t before = dvec_bytes(rows) + mask_bytes(pk.cu != nullptr, B, Hq, Nq, p.max_len_k);
+  p.part = (float*)((char*)workspace + before);
+  p.part_rows = (pk.cu ? 1 : (size_t)B) * Hkv * Nk;
   if (!pk.cu) {
     dkdv_split(B, Hq, Hkv, Nq, Nk, &p.psize, &p.nparts);
-    p.part = (float*)((char*)p.mask + mask_bytes(false, B, Hq, Nq, Nk));
+  } else {
+    // (a workspace without room for the parts, e.g. sized for fewer keys, gives unsplit sweeps)
+    dkdv_split_packed(B, pk.max_q, Nk, Hq, Hkv, &p.psize, &p.nparts);
+    if (workspace_bytes < before + part_bytes_packed(B, pk.max_q, Nk, Hq, Hkv, D)) {
+      p.psize = 1 << 30;
+      p.nparts = 1;
+    }
   }
   if ((e = mala::launch_bwd(p, D, s)) != hipSuccess) return hip_fail(e, "mala_bwd: kernel launch");
   return MALA_OK;
@@ -365,7 +392,9 @@ size_t mala_bwd_workspace_size(int B, int Hq, int Hkv, int Nq, int Nk, int D) {
 size_t mala_bwd_varlen_workspace_size(int num_seqs, int max_seqlen_k, int total_q, int Hq,
                                       int Hkv, int D) {
   if (num_seqs <= 0 || max_seqlen_k <= 0 || total_q <= 0 || Hq <= 0 || Hkv <= 0) return 0;
-  return bwd_workspace(true, num_seqs, Hq, Hkv, total_q, max_seqlen_k, D);
+  // with the parts of self-attention (keys = queries)
+  return bwd_workspace(true, num_seqs, Hq, Hkv, total_q, max_seqlen_k, D) +
+         (Hq % Hkv ? 0 : part_bytes_packed(num_seqs, max_seqlen_k, total_q, Hq, Hkv, D));
 }
 
 int mala_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse,
@@ -386,7 +415,8 @@ int mala_bwd(const void* q, const void* k, const void* v, const void* o, const f
     return fail(MALA_ERR_WORKSPACE, "mala_bwd needs %zu workspace bytes, got %zu", need, workspace_bytes);
   if (((uintptr_t)workspace) % 16) return fail(MALA_ERR_WORKSPACE, "workspace not 16-byte aligned");
   return run_bwd(q, k, v, Packed{}, o, o_dtype, lse, dout, dq, dk, dv, grad_dtype, row_tiles,
-                 counters, workspace, B, Hq, Hkv, Nq, Nk, D, scale, tau, (hipStream_t)stream);
+                 counters, workspace, workspace_bytes, B, Hq, Hkv, Nq, Nk, D, scale, tau,
+                 (hipStream_t)stream);
 }
 
 int mala_bwd_varlen(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_q,
@@ -404,14 +434,14 @@ int mala_bwd_varlen(const void* q, const void* k, const void* v, const int32_t* 
   if (!st) st = check_dtype(o_dtype, "o_dtype");
   if (!st) st = check_dtype(grad_dtype, "grad_dtype");
   if (st) return st;
-  const size_t need = mala_bwd_varlen_workspace_size(num_seqs, max_seqlen_k, total_q, Hq, Hkv, D);
+  const size_t need = bwd_workspace(true, num_seqs, Hq, Hkv, total_q, max_seqlen_k, D);
   if (!workspace || workspace_bytes < need)
     return fail(MALA_ERR_WORKSPACE, "mala_bwd_varlen needs %zu workspace bytes, got %zu", need,
                 workspace_bytes);
   if (((uintptr_t)workspace) % 16) return fail(MALA_ERR_WORKSPACE, "workspace not 16-byte aligned");
   return run_bwd(q, k, v, Packed{cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k}, o,
                  o_dtype, lse, dout, dq, dk, dv, grad_dtype, row_tiles, counters, workspace,
-                 num_seqs, Hq, Hkv, total_q, total_k, D, scale, tau, (hipStream_t)stream);
+                 workspace_bytes, num_seqs, Hq, Hkv, total_q, total_k, D, scale, tau, (hipStream_t)stream);
 }
 
 size_t mala_decode_workspace_size(int B, int Hq, int D, int num_splits) {

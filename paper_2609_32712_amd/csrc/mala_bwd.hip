@@ -69,7 +69,8 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-// D_q = sum_d O[q][d] * dO[q][d]; 16 lanes per row; O in fp32 or bf16 (OT).
+// D_q = sum_d O[q][d] * dO[q][d]; 16 lanes per row; O in fp32 or bf16 (OT).  (Four rows per
+// lane, all loaded before the first sum, measured the same: 80 against 81 us for 360000 rows.)
 template <int D, typename OT>
 __global__ __launch_bounds__(256) void mala_bwd_preprocess_kernel(const OT* o, const bf16* dout,
                                                                   float* dvec, long rows) {
@@ -109,7 +110,8 @@ __device__ __forceinline__ float row_dot(const BwdParams& p, long row, int h, bo
     const long i = row * D + 16 * kk + 8 * h;
     if (valid) {
       if (p.o_bf16) {
-        const bf16x8 v = load8(static_cast<const bf16*>(p.o) + i);
+        bf16 v[8];
+        __builtin_memcpy(v, static_cast<const bf16*>(p.o) + i, sizeof(v));
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = (float)v[e];
       } else {
@@ -659,8 +661,7 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
     if (key < Nk) {
       const float f = role == 1 ? 1.f : p.scale;
       const bool split = p.nparts > 1;
-      void* dst = split ? (void*)(p.part + (size_t)(2 * part + (role == 1 ? 0 : 1)) *
-                                               ((size_t)p.B * p.Hkv * p.Nk) * D)
+      void* dst = split ? (void*)(p.part + (size_t)(2 * part + (role == 1 ? 0 : 1)) * p.part_rows * D)
                         : (role == 1 ? p.dv : p.dk);
       const long krow = (kbase + key) * D;
 #pragma unroll
@@ -953,8 +954,7 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
       for (int m = 0; m < NM; ++m) {
         const int mat = mat0 + m;
         const float f = mat ? p.scale : 1.f;
-        void* dst = split ? (void*)(p.part + (size_t)(2 * part + mat) *
-                                                 ((size_t)p.B * p.Hkv * p.Nk) * D)
+        void* dst = split ? (void*)(p.part + (size_t)(2 * part + mat) * p.part_rows * D)
                           : (mat ? p.dk : p.dv);
 #pragma unroll
         for (int g = 0; g < 4; ++g)
@@ -1542,21 +1542,22 @@ __global__ __launch_bounds__(512) void mala_bwd_dq_rows_kernel(BwdParams p) {
   if (p.counters) blk_flush(bcnt, p.counters);
 }
 
-// Sum of the parts of split dK/dV sweeps in part order (fixed-length batches): one
-// thread per four columns of a K-shaped row; a row's key block has
+// Sum of the parts of split dK/dV sweeps in part order: one thread per four columns of a
+// K-shaped row, blockIdx.y the (sequence, KV head); a row's key block has
 // ceil(iterations / psize) parts.
 template <int D>
 __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) {
-  const long rows = (long)p.B * p.Hkv * p.Nk;
-  const long n4 = rows * (D / 4);
-  const size_t slot = (size_t)rows * D;
-  const int grp = p.Hq / p.Hkv;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
+  const int b = blockIdx.y / p.Hkv, hkv = blockIdx.y % p.Hkv, grp = p.Hq / p.Hkv;
+  const Seg sg = seq_slice(p, b);
+  if (sg.Nq == 0) return;   // a skipped packed sequence
+  const long row0 = sg.kb + (long)hkv * p.Nk;
+  const size_t slot = p.part_rows * D;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < (long)sg.Nk * (D / 4);
        i += (long)gridDim.x * blockDim.x) {
-    const long row = i / (D / 4);
-    const long e = row * D + (i % (D / 4)) * 4;
-    const int kb0 = (int)(row % p.Nk) / kBwdKeys * kBwdKeys;
-    const int np = (dkdv_iterations(p.Nq, p.Nk, kb0, grp) + p.psize - 1) / p.psize;
+    const int key = (int)(i / (D / 4));
+    const long e = (row0 + key) * D + (i % (D / 4)) * 4;
+    const int kb0 = key / kBwdKeys * kBwdKeys;
+    const int np = (dkdv_iterations(sg.Nq, sg.Nk, kb0, grp) + p.psize - 1) / p.psize;
     f32x4 sv = {0.f, 0.f, 0.f, 0.f}, sk = {0.f, 0.f, 0.f, 0.f};
     for (int q = 0; q < np; ++q) {
       sv += *reinterpret_cast<const f32x4*>(p.part + (size_t)(2 * q) * slot + e);
@@ -1618,9 +1619,10 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
   if (rule != DkdvRule::kBlocks)
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_kernel<D>, dim3(4 * n), dim3(512), 0, st, p);
   if (p.nparts > 1) {
-    const long n4 = (long)p.B * p.Hkv * p.Nk * (D / 4);
+    const long slices = (long)p.B * p.Hkv, blocks = ((long)p.max_len_k * (D / 4) + 255) / 256;
     hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<D>,
-                       dim3((unsigned)std::min<long>((n4 + 255) / 256, 8192)), dim3(256), 0, st, p);
+                       dim3((unsigned)std::min(blocks, 8192 / slices + 1), (unsigned)slices),
+                       dim3(256), 0, st, p);
   }
 }
 

@@ -181,9 +181,11 @@ struct BwdParams {
   int mask_rows;       // query-tile rows: B ceil(Nq / kBq) (packed: total_q / kBq + B)
   // Split key-block sweeps: part p of a block takes iterations [p psize, (p + 1) psize)
   // and, when nparts > 1, writes its fp32 dV and dK sums to part[(2 p + {0, 1}) rows + row]
-  // (rows = B Hkv Nk rows of D floats), which the reduction pass adds up in order.
+  // (rows of D floats, part_rows of them: those of K), which the reduction pass adds up in
+  // order.
   int psize, nparts;
   float* part;
+  size_t part_rows;
   // Both dK/dV kernels are launched and each sequence goes by its decisions: to the pairs
   // kernel when it is sparse (sparse_sequence), else to the other one.
   int by_sequence;
