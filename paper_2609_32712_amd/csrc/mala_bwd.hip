@@ -1579,11 +1579,13 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
 // workgroup: under 2% of sweeps of 512 iterations and more.  8 x 4096 language-model-like
 // tokens at tau = 1: 872 / 522.
 constexpr float kSparseLog2Tau = -3.33f;   // log2 of 0.1: tolerances that may skip many tiles
+constexpr long kPairsGridMax = 16384;       // 128-key sweeps, four workgroups each
 enum class DkdvRule { kPairs, kBlocks, kBySequence };
 static DkdvRule dkdv_rule(const BwdParams& p) {
-  long n = (long)p.nkblk * p.B * p.Hkv;
-  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B));
-  n *= p.nparts;
+  const long grid = (long)p.nkblk * p.B * p.Hkv * p.nparts;
+  if (grid > kPairsGridMax) return DkdvRule::kBlocks;   // packed batches: mostly empty workgroups
+  long n = grid;
+  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
   if (n <= kNumCus) return DkdvRule::kPairs;
   const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
   return p.log2tau >= kSparseLog2Tau && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
@@ -1601,8 +1603,8 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
   // 32 heads 2048 238 / 298.  At tau = 1, where the other kernel skips for less, 2048
   // language-model-like tokens 177 / 157, 4096 331 / 339)
   if (few_row_blocks(p, p.log2tau >= kSparseLog2Tau ? 2 : 3)) {
-    hipLaunchKernelGGL(mala_bwd_dq_rows_kernel<D>, dim3((unsigned)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq), dim3(512),
-                       0, st, p);
+    const unsigned nqt = (unsigned)((p.max_len + kBq - 1) / kBq);
+    hipLaunchKernelGGL(mala_bwd_dq_rows_kernel<D>, dim3(nqt * p.B * p.Hq), dim3(512), 0, st, p);
   } else {
     // D_q over every row of the q-shaped tensors (packed: all heads x total rows)
     const long rows = (p.cu ? 1l : p.B) * p.Hq * p.Nq;
