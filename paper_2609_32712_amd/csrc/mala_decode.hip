@@ -344,9 +344,11 @@ __global__ __launch_bounds__(W * 64) void mala_decode_team_kernel(DecParams p) {
     }
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
+    // a tile of -inf scores only (masked keys) is retained at tau = 0 and sums to 0, not NaN
+    const float shift = mt == kNegInf ? 0.f : mt;
     float ps = 0.f;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) ps += fast_exp2(sv[r] - mt);
+    for (int r = 0; r < 8; ++r) ps += fast_exp2(sv[r] - shift);
     ps += __shfl_xor(ps, 16);
     ps += __shfl_xor(ps, 32);
     if (g == 0) red[round & 1][w][col] = f32x2{mt, ps};
@@ -374,13 +376,14 @@ __global__ __launch_bounds__(W * 64) void mala_decode_team_kernel(DecParams p) {
     }
     if (wave_any(mine)) {
       float alpha = 1.f;
-      if (mine) {
+      if (mine) {   // the accumulator is 0 until a tile with a finite maximum sets ref
         const float r_new = fmaxf(ref, mt);
-        alpha = fast_exp2(ref - r_new);
+        alpha = r_new == kNegInf ? 1.f : fast_exp2(ref - r_new);
         ref = r_new;
       }
+      const float rs = ref == kNegInf ? 0.f : ref;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) sv[r] = mine ? fast_exp2(sv[r] - ref) : 0.f;
+      for (int r = 0; r < 8; ++r) sv[r] = mine ? fast_exp2(sv[r] - rs) : 0.f;
       bf16x8 ph, pl;
       split_bf16x8(sv, ph, pl);
 #pragma unroll

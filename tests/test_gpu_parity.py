@@ -582,6 +582,32 @@ def test_decode_team_matches_one_wavefront_per_split(Hq, Hkv, N, D, splits, tau)
         assert cb[i] == B * ca[i], i
 
 
+@pytest.mark.parametrize("N,D,splits,B", [(384, 128, 1, 1), (1280, 64, 1, 1), (1312, 128, 2, 1),
+                                         (384, 64, 1, 257)])
+def test_decode_masked_tiles_add_nothing_at_tau0(N, D, splits, B):
+    # Keys at the type's lowest value (a padding mask) have scores of -inf; at tau = 0 their
+    # tiles are retained all the same and must add nothing.  Teams of 4 and 8 wavefronts per
+    # split and (B = 257) one wavefront each.  fp32 scores and sums: the bound of the other
+    # decode comparisons with another summation order, 1e-5, on O of size ~1.
+    g = torch.Generator().manual_seed(7)
+    q = torch.randn(1, 4, D, generator=g).abs().bfloat16()
+    k, v = (torch.randn(1, 1, N, D, generator=g).bfloat16() for _ in range(2))
+    masked = torch.zeros(N, dtype=torch.bool)
+    for t in (3, 7, 8):     # not the last tile of a split, whose state starts from it
+        masked[32 * t:32 * t + 32] = True
+    k[:, :, masked] = torch.finfo(torch.bfloat16).min
+    s = (q[0].double() @ k[0, 0].double().t()) * f32(D ** -0.5)
+    s[:, masked] = -math.inf
+    lse = torch.logsumexp(s, 1)
+    o = torch.exp(s - lse[:, None]) @ v[0, 0].double()
+    x = [a.expand(B, *a.shape[1:]).contiguous().cuda() for a in (q, k, v)]
+    d = mala.decode(*x, f32(D ** -0.5), 0.0, splits)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(host(d["lse"][B - 1]), lse.numpy(), atol=1e-5)
+    np.testing.assert_allclose(host(d["o"][B - 1]), o.numpy(), atol=1e-5)
+    assert (d["head_tiles"] == N // 32).all()
+
+
 def test_decode_splits_cover_dense_at_tau0():
     spec = dict(kind="decode", B=1, Hq=4, Hkv=1, N=2048, D=128, beta=3.0, needles=4)
     w = Workload(spec)
