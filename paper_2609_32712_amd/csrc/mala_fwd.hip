@@ -451,7 +451,6 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
     };
     float m = kNegInf;     // predicted reference
     float sv[16];
-    int moved = 3;         // steps since the last move or resync, as 3, 2, 1, 0
 #pragma unroll
     for (int r = 0; r < 16; ++r) sv[r] = kNegInf;
     // this wavefront's K tile of a stage, to its own LDS slot
@@ -487,7 +486,6 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
       const f32x2 lm = rowlm[pb][c];            // l and m after stage n - 3
       if (__builtin_amdgcn_readfirstlane(resync[pb])) {
         m = lm[1];          // stage n - 3 ended with another reference: through n - 2 from there
-        moved = 3;
 #pragma unroll
         for (int u = 0; u < W; ++u) {
           const float x = redm[(n + 1) % 3][u][c] * p.scale2;
@@ -503,7 +501,6 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
         const float x = mt[u] * p.scale2;
         const bool mv = (n > 0) & wave_any(x > m + 8.f);
         m = mv ? fmaxf(m, x) : m;
-        moved = mv ? 3 : moved;
         mw = wave == u ? m : mw;
       }
       const float ps = fwd_probabilities(sv, p.scale2, mw);
@@ -511,13 +508,14 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
       Ps[pb][wave][0][lane] = p0;
       Ps[pb][wave][1][lane] = p1;
       if (h == 0) redp[pb][wave][c] = f32x2{ps, mw};
-      // the lo terms wherever the test of the tile's share can ask for them: l only grows
-      // while the reference stands
-      if (moved || wave_any(ps > kFwdLoShare * lm[0])) {
+      // The lo terms wherever the test of the tile's share can ask for them.  A tile used
+      // with this P has reference mw, and what l held after stage n - 3 is by then
+      // 2^(lm[1] - mw) of it (the margin is beyond any rounding of the rescalings) and has
+      // only grown since.  (Tiles of another reference are formed again.)
+      if (wave_any(ps > kFwdLoShare * 0.999f * (lm[0] * rescale(lm[1], mw)))) {
         Ps[pb][wave][2][lane] = lo_bf16x8(sv, p0);
         Ps[pb][wave][3][lane] = lo_bf16x8(sv + 8, p1);
       }
-      moved = max(0, moved - 1);
       const float raw = row_max(j, sc, sv);
       if (h == 0) redm[n % 3][wave][c] = raw;
       wait_vm_keep<NKL>();                      // this wavefront's V loads have landed

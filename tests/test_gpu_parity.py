@@ -1070,6 +1070,40 @@ def test_small_grid_forward_gives_the_same_bits(B, Hq, Hkv, Nq, Nk, D):
             assert torch.equal(x, y), (tau, name)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_small_grid_forward_after_a_skipped_tile_moved_the_reference(D):
+    # tau > 1 can skip a tile whose maximum is 2^8 above a row's reference.  From the last
+    # key tile down: one tile at score 0 (base 2), six at 8 (the first five retained), one
+    # at 8.0625 that every row skips, low ones, and long after it (idx 25) a tile with the
+    # very same maximum, retained for row 30's sake.  That tile's P needs its low bf16 term,
+    # since the rows' normalizers have just shrunk by 2^8.
+    T, Nq = 28, 32
+    Nk = 32 * T
+    q, k = torch.zeros(1, 1, Nq, D), torch.zeros(1, 1, Nk, D)
+    q[..., 0] = 1.0
+    q[0, 0, 30] = 0.0
+    q[0, 0, 30, 1] = 1.0
+    g = torch.Generator().manual_seed(3)
+    for idx in range(T):
+        kt = k[0, 0, 32 * (T - 1 - idx):32 * (T - idx)]
+        kt[:, 0] = 0.0 if idx == 0 else 8.0 if idx < 7 else -20.0
+        kt[:, 1] = 0.0 if idx == 0 else -20.0
+        if idx == 7:
+            kt[:, 0] = 8.0625
+        if idx == 25:
+            kt[:, 0] = 8.0625 - torch.randint(0, 8, (32,), generator=g) / 16
+            kt[5, 0] = 8.0625
+            kt[9, 1] = -1.5
+    v = torch.randn(1, 1, Nk, D, generator=g)
+    q, k, v = (x.bfloat16().cuda() for x in (q, k, v))
+    s, tau = f32(math.log(2.0)), f32(Nk * 2.0 ** -7.02)
+    a, b = (mala.fwd(q, k, v, s, tau, stats=st) for st in (True, False))
+    torch.cuda.synchronize()
+    # the first six tiles and idx 25, for every row of the tile
+    assert (a["row_tiles"] == 7).all()
+    assert torch.equal(a["o"], b["o"]) and torch.equal(a["lse"], b["lse"])
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,D,tau,needle_block", [
     (33, 2, 2, 500, 64, 1e-3, 1), (17, 4, 2, 1025, 128, 1e-3, 1), (17, 4, 2, 993, 128, 1.0, 32),
     (129, 2, 1, 129, 128, 0.0, 1), (5, 8, 2, 4065, 128, 1.0, 32), (5, 8, 2, 4096, 64, 1.0, 1),
