@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void mala_bwd_preprocess_kernel(const OT* o, c
     const OT* op = o + row * D + part * PER;
     const bf16* dp = dout + row * D + part * PER;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) s += (float)op[e] * (float)dp[e];
+    for (int e = 0; e < PER; ++e) s = __builtin_fmaf((float)op[e], (float)dp[e], s);
   }
 #pragma unroll
   for (int w = 8; w >= 1; w >>= 1) s += __shfl_xor(s, w, 16);
@@ -98,7 +98,7 @@ static void launch_preprocess(const OT* o, const BwdParams& p, long rows, hipStr
 // The same D_q, bit for bit, for the query row (row index row of the q-shaped tensors) whose
 // dO a lane of the transposed products holds as the operand ob: the sums of the kernel
 // above's 16 parts of D / 16 columns, two halves of which lie in the lane pair (h), added
-// in its order (parts 8, 4, 2, 1 apart).
+// in its order (parts 8, 4, 2, 1 apart); both write their fused products out.
 template <int D>
 __device__ __forceinline__ float row_dot(const BwdParams& p, long row, int h, bool valid,
                                          const bf16x8 (&ob)[D / 16]) {
@@ -123,7 +123,7 @@ __device__ __forceinline__ float row_dot(const BwdParams& p, long row, int h, bo
     for (int x = 0; x < NP; ++x) {
       float s = 0.f;
 #pragma unroll
-      for (int e = 0; e < PER; ++e) s += o[PER * x + e] * (float)ob[kk][PER * x + e];
+      for (int e = 0; e < PER; ++e) s = __builtin_fmaf(o[PER * x + e], (float)ob[kk][PER * x + e], s);
       a[kk][x] = s;
     }
   }

@@ -28,20 +28,22 @@
 
 namespace mala {
 
-// The two forward kernels below give the same bits: they share the order of every sum
-// and, through these functions (no contraction, fused operations written out), the
-// rounding of every row quantity.
+// The two forward kernels below give the same bits: they share the order of every sum,
+// and neither leaves the rounding of a row quantity to the compiler: contraction is off
+// and fused operations are written out, in the functions here and in both kernels.
 
-// log2(tau / L_q) of query row q (L_q = q + 1 + off).
-__device__ __forceinline__ float row_threshold(float log2tau, long q, long off) {
+// -log2(tau / L_q) of query row q (L_q = q + 1 + off).
+__device__ __forceinline__ float row_threshold(float log2tau, int q, long off) {
 #pragma clang fp contract(off)
-  return log2tau - log2f((float)(q + 1 + off));
+  return log2f((float)(q + 1 + off)) - log2tau;
 }
 // The online test of a row whose largest raw score in the tile is raw: the tile's
-// largest scaled score against log2 of the retained normalizer l (reference m).
-__device__ __forceinline__ bool online_demand(float raw, float scale2, float m, float l, float thr) {
+// largest scaled score against log2 of the retained normalizer l (reference m), both sides
+// negated: so -m need not be kept in a register, and the 256-row kernel is the instruction
+// stream that the compiler made of mt - m - log2(l) >= thr by contraction.
+__device__ __forceinline__ bool online_demand(float raw, float scale2, float m, float l, float nthr) {
 #pragma clang fp contract(off)
-  return (l == 0.f) | (__builtin_fmaf(raw, scale2, -m) - fast_log2(l) >= thr);
+  return (l == 0.f) | (__builtin_fmaf(raw, -scale2, m) + fast_log2(l) <= nthr);
 }
 // Scores of a tile's key rows ka against the wavefront's query rows, k-steps in order.
 template <int KS>
@@ -77,6 +79,7 @@ __device__ __forceinline__ float masked_max(const f32x16& s, bool need_mask, int
 // as a tree (over both halves of the column).  A row with no legal key so far keeps
 // m = -inf: shift by 0 so that exp2(-inf) = 0.
 __device__ __forceinline__ float fwd_probabilities(float (&sv)[16], float scale2, float m) {
+#pragma clang fp contract(off)
   const float shift = (m == kNegInf) ? 0.f : m;
 #pragma unroll
   for (int r = 0; r < 16; ++r) sv[r] = fast_exp2(__builtin_fmaf(sv[r], scale2, -shift));
@@ -92,6 +95,7 @@ __device__ __forceinline__ float rescale(float m, float m_new) {
 
 template <int D>
 __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
+#pragma clang fp contract(off)
   constexpr int NT = kFwdWaves * 64;     // threads per workgroup
   constexpr int KS = D / 16;             // k-steps of the QK product
   constexpr int DB = D / 32;             // 32-wide output column blocks
@@ -144,7 +148,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
   int cnt = 0;          // retained diagonal tiles in which this row has a legal key
   unsigned n_ret_m = 0;  // retained diagonal tiles
-  const float thr = p.log2tau - log2f((float)(qrow + 1 + off));   // log2(tau / L_q)
+  const float nthr = row_threshold(p.log2tau, qrow, off);   // -log2(tau / L_q)
 
   const int qlast_w = min(q0w + kBq - 1, Nq - 1);
   const int jdiag = (q0w < Nq) ? (int)((qlast_w + off) / kBk) : -1;
@@ -238,12 +242,13 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
         }
         // the row max of the raw scores, then scaled (scale2 > 0 and rounding is
         // monotonic, so this is the max of the scaled scores)
-        mt = halves_max(mt) * p.scale2;
+        const float raw = halves_max(mt);
+        mt = raw * p.scale2;
 
         // the online test (rows with no legal key in the tile do not vote); m + log2(l)
         // is log2 of the retained normalizer whichever reference m the row uses
         const bool voter = row_valid & (kb <= qrow + offi);
-        const bool demand = voter & ((l == 0.f) | (mt - m - fast_log2(l) >= thr));
+        const bool demand = voter & online_demand(raw, p.scale2, m, l, nthr);
         if (!wave_any(demand)) continue;    // skipped: m, l and O unchanged
         ++n_ret;
         // off the diagonal every valid row votes: those tiles are counted per wavefront
@@ -373,6 +378,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void mala_fwd_kernel(FwdParams p) {
 // step (32-byte pieces of a row per load), a fetch of V by the consumers 1300.
 template <int D>
 __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdParams p) {
+#pragma clang fp contract(off)
   constexpr int W = kRowsTiles, KS = D / 16, DB = D / 32;
   constexpr int STAGE = tile_elems<D>(W * kBk);
   static_assert(DB <= W, "one column block per consumer");
@@ -528,7 +534,7 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
   // consumers
   const int cw = wave - W;
   const int tro = tr_base<D>(4 * h + (t16 >> 2), G & 1, t16);
-  const float thr = row_threshold(p.log2tau, qrow, offi);
+  const float nthr = row_threshold(p.log2tau, qrow, offi);
   float m = kNegInf, l = 0.f;
   f32x16 acc;
 #pragma unroll
@@ -574,7 +580,7 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
         lu += sr[u][0];
         lo |= (wave_any(sr[u][0] > kFwdLoShare * lu) ? 1 : 0) << u;
       }
-      const float need = thr + 0.01f + (mm + fast_log2(lu));
+      const float need = 0.01f - nthr + (mm + fast_log2(lu));
       bool all = (jtop <= jdiag) & (differ == 0);
 #pragma unroll
       for (int u = 0; u < W; ++u)
@@ -618,7 +624,7 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
           const bool voter = lim + kBk * u >= 0;
           const float rw = redm[rm][u][c];
           const f32x2 pr = redp[pb][u][c];
-          if (!wave_any(voter & online_demand(rw, p.scale2, m, l, thr))) continue;
+          if (!wave_any(voter & online_demand(rw, p.scale2, m, l, nthr))) continue;
           const float x = rw * p.scale2;
           if (wave_any(x > m + 8.f)) {
             const float m_new = fmaxf(m, x);
