@@ -41,51 +41,15 @@ size_t mask_bytes(bool packed, int B, int Hq, int Nq, int max_k) {
   const size_t nkblk = (size_t)(max_k + mala::kBwdKeys - 1) / mala::kBwdKeys;
   return round_up((size_t)Hq * nkblk * mask_rows(packed, B, Nq), 256);
 }
-// Parts of the dK/dV sweeps (fixed-length batches): one per sweep when the key
-// blocks alone give kDkdvSplitGroups workgroups; otherwise parts of the smallest
-// power of two >= kDkdvPartMin iterations that gives at most ~kDkdvSplitGroups
-// parts over all sweeps, so that a long sweep (the first key blocks', or one that
-// retains every tile) no longer sets the kernel's time alone.
-void dkdv_split(int B, int Hq, int Hkv, int Nq, int Nk, int* psize, int* nparts) {
-  const int grp = Hq / Hkv, nkblk = (Nk + mala::kBwdKeys - 1) / mala::kBwdKeys;
-  *psize = 1 << 30;
-  *nparts = 1;
-  if ((long)nkblk * B * Hkv >= mala::kDkdvSplitGroups) return;
-  long total = 0;
-  for (int j = 0; j < nkblk; ++j) total += mala::dkdv_iterations(Nq, Nk, j * mala::kBwdKeys, grp);
-  total *= (long)B * Hkv;
-  const int longest = mala::dkdv_iterations(Nq, Nk, 0, grp);
-  long ps = mala::kDkdvPartMin;
-  while (ps * 2 * mala::kDkdvSplitGroups <= total) ps *= 2;
-  if (ps >= longest) return;
-  *psize = (int)ps;
-  *nparts = (int)((longest + ps - 1) / ps);
-}
-// Packed batches, whose lengths only the device knows: the same rule on what the host
-// knows, blocks of the total and sweeps up to the longest sequence's, half of it long on
-// average.  A sequence of at most psize iterations stays in one part.
-void dkdv_split_packed(int num_seqs, int max_q, int total_k, int Hq, int Hkv, int* psize,
-                       int* nparts) {
-  const long blocks = (long)Hkv * (total_k / mala::kBwdKeys + num_seqs);
-  const long longest = (long)(Hq / Hkv) * ((max_q + mala::kBq - 1) / mala::kBq);
-  *psize = 1 << 30;
-  *nparts = 1;
-  if (blocks >= mala::kDkdvSplitGroups) return;
-  long ps = mala::kDkdvPartMin;
-  while (ps * 4 * mala::kDkdvSplitGroups <= blocks * longest) ps *= 2;
-  if (ps >= longest) return;
-  *psize = (int)ps;
-  *nparts = (int)((longest + ps - 1) / ps);
-}
 size_t part_bytes_packed(int num_seqs, int max_q, int total_k, int Hq, int Hkv, int D) {
   int psize, nparts;
-  dkdv_split_packed(num_seqs, max_q, total_k, Hq, Hkv, &psize, &nparts);
+  mala::dkdv_split_packed(num_seqs, max_q, total_k, Hq, Hkv, &psize, &nparts);
   return nparts > 1 ? round_up((size_t)nparts * 2 * Hkv * total_k * D * sizeof(float), 256) : 0;
 }
 // fp32 partial dV and dK of every part of the split sweeps (fixed-length batches)
 size_t part_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D) {
   int psize, nparts;
-  dkdv_split(B, Hq, Hkv, Nq, Nk, &psize, &nparts);
+  mala::dkdv_split(B, Hq, Hkv, Nq, Nk, &psize, &nparts);
   return nparts > 1 ? round_up((size_t)nparts * 2 * B * Hkv * Nk * D * sizeof(float), 256) : 0;
 }
 size_t bwd_workspace(bool packed, int B, int Hq, int Hkv, int Nq, int max_k, int D) {
@@ -231,11 +195,11 @@ int run_bwd(const void* q, const void* k, const void* v, const Packed& pk,
   p.part = (float*)((char*)workspace + before);
   p.part_rows = (pk.cu ? 1 : (size_t)B) * Hkv * Nk;
   if (!pk.cu) {
-    dkdv_split(B, Hq, Hkv, Nq, Nk, &p.psize, &p.nparts);
+    mala::dkdv_split(B, Hq, Hkv, Nq, Nk, &p.psize, &p.nparts);
   } else {
     // a workspace without room for the parts (e.g. sized for fewer keys), or a batch of so
     // many sequences that most of the parts' workgroups would find none, gives whole sweeps
-    dkdv_split_packed(B, pk.max_q, Nk, Hq, Hkv, &p.psize, &p.nparts);
+    mala::dkdv_split_packed(B, pk.max_q, Nk, Hq, Hkv, &p.psize, &p.nparts);
     if (workspace_bytes < before + part_bytes_packed(B, pk.max_q, Nk, Hq, Hkv, D) ||
         (long)p.nkblk * B * Hkv * p.nparts > 16384) {
       p.psize = 1 << 30;

@@ -1578,19 +1578,6 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
 // promise.  Both kernels are then launched and one of them leaves at once, at ~1.2 us per
 // workgroup: under 2% of sweeps of 512 iterations and more.  8 x 4096 language-model-like
 // tokens at tau = 1: 872 / 522.
-constexpr float kSparseLog2Tau = -3.33f;   // log2 of 0.1: tolerances that may skip many tiles
-constexpr long kPairsGridMax = 16384;       // 128-key sweeps, four workgroups each
-enum class DkdvRule { kPairs, kBlocks, kBySequence };
-static DkdvRule dkdv_rule(const BwdParams& p) {
-  const long grid = (long)p.nkblk * p.B * p.Hkv * p.nparts;
-  if (grid > kPairsGridMax) return DkdvRule::kBlocks;   // packed batches: mostly empty workgroups
-  long n = grid;
-  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
-  if (n <= kNumCus) return DkdvRule::kPairs;
-  const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
-  return p.log2tau >= kSparseLog2Tau && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
-}
-
 template <int D>
 static void launch_bwd_t(BwdParams p, hipStream_t st) {
   dim3 grid_q((unsigned)p.nqblk * p.B * p.Hq), block_q(kDqWaves * 64);

@@ -1,0 +1,106 @@
+// Host-side rules of the launches: which kernel a call takes and how its sweeps are split.
+// Plain C++ on the sizes of a call (P: FwdParams, BwdParams, or a test's stand-in for them).
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <numeric>
+
+namespace mala {
+
+// Decision geometry (shared by forward and backward so that the backward
+// support nests inside the forward support; decode uses 1 x kDecBk).
+constexpr int kBq = 32;      // query rows per decision tile = rows of one wavefront
+constexpr int kBk = 32;      // keys per decision tile
+constexpr int kBwdKeys = 128;                // keys per block of the dK/dV pass (4 key groups x kBk)
+constexpr int kNumCus = 256;                 // compute units of an MI355X
+// Below kDkdvSplitGroups key-block workgroups (batch x KV heads x key blocks) the
+// dK/dV sweeps are split into parts of at least kDkdvPartMin iterations, run by
+// workgroups of their own, and summed by a reduction pass.
+constexpr int kDkdvSplitGroups = 1024;
+constexpr int kDkdvPartMin = 512;
+constexpr float kSparseLog2Tau = -3.33f;     // log2 of 0.1: tolerances that may skip many tiles
+
+// Iterations of the dK/dV sweep of the key block starting at key kb0 of a sequence
+// (Nq query rows, the last aligned with the last of Nk keys): every (query tile, head
+// of the GQA group) from the last query tile down to the block's diagonal.
+constexpr int dkdv_iterations(int Nq, int Nk, int kb0, int grp) {
+  const long first_q = (long)kb0 - ((long)Nk - Nq);
+  const int qi_start = first_q <= 0 ? 0 : (int)(first_q / kBq);
+  return grp * ((Nq + kBq - 1) / kBq - qi_start);
+}
+
+// Parts of the dK/dV sweeps (fixed-length batches): one per sweep when the key
+// blocks alone give kDkdvSplitGroups workgroups; otherwise parts of the smallest
+// power of two >= kDkdvPartMin iterations that gives at most ~kDkdvSplitGroups
+// parts over all sweeps, so that a long sweep (the first key blocks', or one that
+// retains every tile) no longer sets the kernel's time alone.
+inline void dkdv_split(int B, int Hq, int Hkv, int Nq, int Nk, int* psize, int* nparts) {
+  const int grp = Hq / Hkv, nkblk = (Nk + kBwdKeys - 1) / kBwdKeys;
+  *psize = 1 << 30;
+  *nparts = 1;
+  if ((long)nkblk * B * Hkv >= kDkdvSplitGroups) return;
+  long total = 0;
+  for (int j = 0; j < nkblk; ++j) total += dkdv_iterations(Nq, Nk, j * kBwdKeys, grp);
+  total *= (long)B * Hkv;
+  const int longest = dkdv_iterations(Nq, Nk, 0, grp);
+  long ps = kDkdvPartMin;
+  while (ps * 2 * kDkdvSplitGroups <= total) ps *= 2;
+  if (ps >= longest) return;
+  *psize = (int)ps;
+  *nparts = (int)((longest + ps - 1) / ps);
+}
+// Packed batches, whose lengths only the device knows: the same rule on what the host
+// knows, blocks of the total and sweeps up to the longest sequence's, half of it long on
+// average.  A sequence of at most psize iterations stays in one part.
+inline void dkdv_split_packed(int num_seqs, int max_q, int total_k, int Hq, int Hkv, int* psize,
+                              int* nparts) {
+  const long blocks = (long)Hkv * (total_k / kBwdKeys + num_seqs);
+  const long longest = (long)(Hq / Hkv) * ((max_q + kBq - 1) / kBq);
+  *psize = 1 << 30;
+  *nparts = 1;
+  if (blocks >= kDkdvSplitGroups) return;
+  long ps = kDkdvPartMin;
+  while (ps * 4 * kDkdvSplitGroups <= blocks * longest) ps *= 2;
+  if (ps >= longest) return;
+  *psize = (int)ps;
+  *nparts = (int)((longest + ps - 1) / ps);
+}
+
+// The dK/dV kernels of a call: pairs (all sweeps), blocks (all sweeps), or each sequence by
+// the tiles that the dQ pass retained.
+enum class DkdvRule { kPairs, kBlocks, kBySequence };
+constexpr long kPairsGridMax = 16384;        // 128-key sweeps, four workgroups each
+
+template <class P>
+inline DkdvRule dkdv_rule(const P& p) {
+  const long grid = (long)p.nkblk * p.B * p.Hkv * p.nparts;
+  if (grid > kPairsGridMax) return DkdvRule::kBlocks;   // packed batches: mostly empty workgroups
+  long n = grid;
+  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
+  if (n <= kNumCus) return DkdvRule::kPairs;
+  const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
+  return p.log2tau >= kSparseLog2Tau && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
+}
+
+// Whether a call's time is the chain of one row block's key tiles and not the chip's
+// throughput, so that the kernels of one workgroup per 32 query rows (the forward's and
+// the dQ pass's) are ahead of those of 256 rows.  In units of one step of the former (four
+// key tiles, ~1.1 us) its row blocks take the mean of (stages + 3) each over the CUs; the
+// chain of the latter takes `chain` such units per stage of the longest block.  Packed
+// batches hold at most total / 32 + sequences row blocks, taken as long as the longest.
+constexpr int kRowsTiles = 4;   // key tiles per stage of those kernels
+template <class P>
+inline bool few_row_blocks(const P& p, int chain) {
+  const long stage = kRowsTiles * kBk;
+  const long longest = (p.max_len_k + stage - 1) / stage;
+  const long grid = (long)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq;
+  long blocks = grid;
+  if (p.cu && (long)p.Hq * (p.Nq / kBq + p.B) < grid) blocks = (long)p.Hq * (p.Nq / kBq + p.B);
+  if (grid > 16 * kNumCus) return false;
+  if (blocks <= kNumCus) return true;
+  const long shortest = (p.max_len_k - p.max_len) / stage + 1;
+  const long mean2 = p.cu ? 2 * longest : shortest + longest;   // twice the mean
+  return blocks * (mean2 + 6) <= 2l * chain * kNumCus * longest;
+}
+
+}  // namespace mala

@@ -3,27 +3,17 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mala_dispatch.h"
+
 namespace mala {
 
-// Decision geometry (shared by forward and backward so that the backward
-// support nests inside the forward support; decode uses 1 x kDecBk).
-constexpr int kBq = 32;      // query rows per decision tile = rows of one wavefront
-constexpr int kBk = 32;      // keys per decision tile
-constexpr int kDecBk = 32;   // keys per decode decision tile
-
-constexpr int kNumCus = 256;                 // compute units of an MI355X
+constexpr int kDecBk = 32;                   // keys per decode decision tile
 constexpr int kFwdWaves = 8;                 // wavefronts per forward workgroup (2 per SIMD)
 constexpr int kFwdRows = kFwdWaves * kBq;    // 256 query rows per workgroup
 constexpr int kDqWaves = 8;                  // wavefronts per dQ workgroup (2 per SIMD)
 constexpr int kDqRows = kDqWaves * kBq;      // 256 query rows per workgroup
 constexpr int kFwdStage = 64;                // keys per K/V stage in LDS (forward and dQ)
-constexpr int kBwdKeys = 128;                // keys per dK/dV workgroup (4 key groups x kBk)
 constexpr int kDkdvChunk = 4096;             // sweep iterations the dK/dV kernel compacts at once
-// Below kDkdvSplitGroups key-block workgroups (batch x KV heads x key blocks) the
-// dK/dV sweeps are split into parts of at least kDkdvPartMin iterations, run by
-// workgroups of their own, and summed by a reduction pass (fixed-length batches).
-constexpr int kDkdvSplitGroups = 1024;
-constexpr int kDkdvPartMin = 512;
 // Budgets of the low bf16 term in the backward.  P and dS enter the MFMAs as
 // hi + lo (two bf16 terms, 2^-16 relative).  The lo term of a tile is left out of
 // dV (P) or dK (dS) while, for every key of the tile, the P mass or the sum of |dS|
@@ -114,27 +104,6 @@ __device__ __forceinline__ Seg seq_slice(const P& p, int b) {
   return Seg{p.Nq, p.Nk, (long)b * p.Hq * p.Nq, (long)b * p.Hkv * p.Nk};
 }
 
-// Whether a call's time is the chain of one row block's key tiles and not the chip's
-// throughput, so that the kernels of one workgroup per 32 query rows (the forward's and
-// the dQ pass's) are ahead of those of 256 rows.  In units of one step of the former (four
-// key tiles, ~1.1 us) its row blocks take the mean of (stages + 3) each over the CUs; the
-// chain of the latter takes `chain` such units per stage of the longest block.  Packed
-// batches hold at most total / 32 + sequences row blocks, taken as long as the longest.
-constexpr int kRowsTiles = 4;   // key tiles per stage of those kernels
-template <class P>
-inline bool few_row_blocks(const P& p, int chain) {
-  const long stage = kRowsTiles * kBk;
-  const long longest = (p.max_len_k + stage - 1) / stage;
-  const long grid = (long)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq;
-  long blocks = grid;
-  if (p.cu && (long)p.Hq * (p.Nq / kBq + p.B) < grid) blocks = (long)p.Hq * (p.Nq / kBq + p.B);
-  if (grid > 16 * kNumCus) return false;
-  if (blocks <= kNumCus) return true;
-  const long shortest = (p.max_len_k - p.max_len) / stage + 1;
-  const long mean2 = p.cu ? 2 * longest : shortest + longest;   // twice the mean
-  return blocks * (mean2 + 6) <= 2l * chain * kNumCus * longest;
-}
-
 struct FwdParams {
   const __bf16* q;
   const __bf16* k;
@@ -190,15 +159,6 @@ struct BwdParams {
   // kernel when it is sparse (sparse_sequence), else to the other one.
   int by_sequence;
 };
-
-// Iterations of the dK/dV sweep of the key block starting at key kb0 of a sequence
-// (Nq query rows, the last aligned with the last of Nk keys): every (query tile, head
-// of the GQA group) from the last query tile down to the block's diagonal.
-__host__ __device__ inline int dkdv_iterations(int Nq, int Nk, int kb0, int grp) {
-  const long first_q = (long)kb0 - ((long)Nk - Nq);
-  const int qi_start = first_q <= 0 ? 0 : (int)(first_q / kBq);
-  return grp * ((Nq + kBq - 1) / kBq - qi_start);
-}
 
 // Byte of the decisions of query-tile row `row` (mask_row0 + query tile), query head
 // hq and key block jb: the key blocks of one row and head are contiguous.
