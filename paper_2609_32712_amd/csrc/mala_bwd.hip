@@ -284,6 +284,7 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   const long off = (long)Nk - Nq;
   const int kb0 = kblk * kBwdKeys;
   if (kb0 >= Nk || Nq == 0) return;        // past the end of (or a skipped) packed sequence
+  if (BYSEQ && sequence_is_sparse(p, mask_row0(p, b, sg))) return;
   const long kbase = sg.kb + (long)hkv * p.Nk;   // key 0 of this (sequence, KV head)
   const int kw = kb0 + grp_k * kBk;        // first key of this wavefront's decision tile
   const int key = kw + c;                  // this lane's key (C-layout column)
@@ -297,9 +298,6 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   const int it0 = part * p.psize, it1 = min(total, it0 + p.psize);
   if (it0 >= total) return;
   const float budget_share = 1.f / (float)((total + p.psize - 1) / p.psize);
-  if (BYSEQ &&
-      sparse_sequence<1024>(p, nqt, off, mask_row0(p, b, sg), reinterpret_cast<longlong2*>(Qs)))
-    return;
   if (p.counters) blk_init(bcnt);
 
   // Query tiles are swept from the last one down to the block's diagonal, the
@@ -701,7 +699,7 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
 // four wavefronts alone 10-15% faster than 128 keys per workgroup, with tiles staged three
 // steps ahead and the next tile's MFMAs under this one's vector work no more than that.
 template <int D>
-__global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
+__device__ __forceinline__ void dkdv_pairs(const BwdParams& p, int item, const Seg sg) {
   constexpr int KS = D / 16;       // k-steps over head_dim
   constexpr int DB = D / 32;       // 32-wide column blocks
   constexpr int RC = D / 8 + 1;                     // 16-byte chunk positions per LDS row
@@ -726,13 +724,12 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, c = lane & 31, G = lane >> 4, t16 = lane & 15;
   const int BHk = p.B * p.Hkv;
-  constexpr int NS = kBwdKeys / kBk;               // workgroups per block of 128 keys
-  const int part = blockIdx.x / (p.nkblk * BHk * NS);   // part of the sweep (split sweeps)
-  const int bhk = blockIdx.x % BHk;
-  const int kx = (blockIdx.x / BHk) % (p.nkblk * NS);   // ascending: the longest sweeps first
+  constexpr int NS = kBwdKeys / kBk;               // items per block of 128 keys
+  const int part = item / (p.nkblk * BHk * NS);    // part of the sweep (split sweeps)
+  const int bhk = item % BHk;
+  const int kx = (item / BHk) % (p.nkblk * NS);    // ascending: the longest sweeps first
   const int kblk = kx / NS, sub = kx % NS;
   const int b = bhk / p.Hkv, hkv = bhk % p.Hkv, grp = p.Hq / p.Hkv;
-  const Seg sg = seq_slice(p, b);
   const int Nq = sg.Nq, Nk = sg.Nk;
   const long off = (long)Nk - Nq;
   const int kb0 = kblk * kBwdKeys, kw = kb0 + sub * kBk;   // first key of the block / workgroup
@@ -746,8 +743,6 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
   if (it0 >= total) return;
   const float budget_share = 1.f / (float)((total + p.psize - 1) / p.psize);
   const int mrow0 = mask_row0(p, b, sg);
-  if (p.by_sequence && !sparse_sequence<512>(p, nqt, off, mrow0, reinterpret_cast<longlong2*>(Qs)))
-    return;
   if (p.counters) blk_init(bcnt);
 
   // The processed iterations of [c0, c0 + CHUNK) into plist, PER per thread, placed by a
@@ -760,7 +755,7 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
       const int it = c0 + PER * tid + u;
       const int dec = it < it1 ? (int)p.mask[mask_index(p, mrow0 + nqt - 1 - it / grp,
                                                          hkv * grp + it % grp, kblk)] : 0;
-      n_do += dec != 0;
+      n_do += (dec & ~kSparseBit) != 0;
       bits |= ((dec >> sub) & 1) << u;
       cnt += (dec >> sub) & 1;
     }
@@ -1017,6 +1012,96 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
   }
   // every wavefront ends here, after the same number of barriers
   if (p.counters) blk_flush(bcnt, p.counters);
+}
+
+template <int D>
+__global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_kernel(BwdParams p) {
+  dkdv_pairs<D>(p, blockIdx.x, seq_slice(p, blockIdx.x % (p.B * p.Hkv) / p.Hkv));
+}
+
+__device__ __forceinline__ long uniform(long x) {
+  return (long)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32 |
+                (uint32_t)__builtin_amdgcn_readfirstlane((int)x));
+}
+
+// The same for the sparse sequences of a call whose other sequences are the blocks kernel's.
+// A workgroup takes the items blockIdx.x, blockIdx.x + gridDim.x, ...; without a sparse
+// sequence it leaves at once, which still costs ~1.9 us of its CU (LDS holds one at a time).
+// Up to kPairsSparseGrid workgroups, ~8 per CU: with one per item, calls without a sparse
+// sequence paid 41-118 us for 4096-16384 items, 2-6% of the backward (D = 64: 4 x 4096 tokens,
+// 32 heads; packed 16384 + 3 x 64 tokens, 8 heads), now ~15; half as many leave the CUs
+// unevenly loaded (8 x 4096 language-model-like tokens at tau = 1: 520 us with one per item,
+// 529 with 2039, 544 with 1021).  An odd number, so that the parts of a block (a power of two
+// of items apart) do not fall to one workgroup (16384 such tokens: 971 us, 1470 with 1024).
+constexpr unsigned kPairsSparseGrid = 2039;
+template <int D>
+__global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_sparse_kernel(BwdParams p) {
+  const int BHk = p.B * p.Hkv, n = kBwdKeys / kBk * p.nkblk * BHk * p.nparts;
+  const auto sparse = [&](int b, const Seg& sg) {
+    return sg.Nq > 0 && sequence_is_sparse(p, mask_row0(p, b, sg));
+  };
+  unsigned long long any = 0;   // every wavefront by itself: the same answer
+  for (int b0 = 0; b0 < p.B; b0 += 64) {
+    const int b = b0 + (threadIdx.x & 63);
+    any |= __builtin_amdgcn_ballot_w64(b < p.B && sparse(b, seq_slice(p, b)));
+  }
+  if (!any) return;
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    const int b = i % BHk / p.Hkv;
+    Seg sg = seq_slice(p, b);
+    // scalar registers, which the loads of the starts in this loop do not give by themselves
+    sg.Nq = __builtin_amdgcn_readfirstlane(sg.Nq);
+    sg.Nk = __builtin_amdgcn_readfirstlane(sg.Nk);
+    sg.qb = uniform(sg.qb);
+    sg.kb = uniform(sg.kb);
+    if (!sparse(b, sg)) continue;
+    dkdv_pairs<D>(p, i, sg);
+    __syncthreads();   // the next item reuses the shared memory
+  }
+}
+
+// Marks the sequences (one workgroup each) that retain few tiles per step of 128 keys: the
+// pairs kernel takes ~0.5 us per retained tile and key group (two per ~1 us step), the other
+// ~1.14 us per step that any of the four groups takes part in, so the pairs are ahead below
+// ~2.2 tiles per step; the line at 1.65 leaves room for their four times as many list scans
+// and tile loads (backward, other kernel / pairs: 32768 tokens, GQA 8/2, 1.58 tiles per step
+// 4.7 / 3.7 ms; 131072 tokens, 1.74: 69.3 / 72.0 ms).  Judged on 2048 bytes of the dQ pass's
+// decisions, spread over the sequence's query tiles, heads and key blocks and weighted by a
+// tile's legal blocks.
+__global__ __launch_bounds__(512) void mala_bwd_choose_kernel(BwdParams p) {
+  constexpr int NT = 512;
+  __shared__ longlong2 red[NT / 64];
+  const int b = blockIdx.x;
+  const Seg sg = seq_slice(p, b);
+  if (sg.Nq == 0) return;   // a skipped packed sequence
+  const long off = (long)sg.Nk - sg.Nq;
+  const int nqt = (sg.Nq + kBq - 1) / kBq, row0 = mask_row0(p, b, sg);
+  long n_tiles = 0, n_steps = 0;
+#pragma unroll
+  for (int u = 0; u < 2048 / NT; ++u) {
+    const uint32_t i = threadIdx.x + NT * u;
+    const uint32_t r = i * 2654435769u;            // Fibonacci hashing: blocks and heads
+    const int qt = (int)((long)nqt * i >> 11);
+    const int nb = (int)(((long)qt * kBq + off) / kBwdKeys) + 1;   // blocks row qt kBq sees
+    const int jb = (int)((uint64_t)(r & 0xffff) * nb >> 16);
+    const int dec = p.mask[mask_index(p, row0 + qt, (int)((r >> 16) % (uint32_t)p.Hq), jb)];
+    n_tiles += (long)__popc(dec) * nb;
+    n_steps += dec ? nb : 0;
+  }
+#pragma unroll
+  for (int w = 32; w >= 1; w >>= 1) {
+    n_tiles += __shfl_xor(n_tiles, w);
+    n_steps += __shfl_xor(n_steps, w);
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = longlong2{n_tiles, n_steps};
+  __syncthreads();
+  if (threadIdx.x) return;
+  n_tiles = n_steps = 0;
+  for (int w = 0; w < NT / 64; ++w) {
+    n_tiles += red[w].x;
+    n_steps += red[w].y;
+  }
+  if (100 * n_tiles < 165 * n_steps) p.mask[mask_index(p, row0, 0, 0)] |= kSparseBit;
 }
 
 // Offline test of one tile in the transposed C layout of the dQ pass: the lane
@@ -1568,22 +1653,11 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
   }
 }
 
-// The dK/dV kernel of a call.  n: sweeps of 128-key blocks (or their parts).  Where they
-// leave CUs idle the chain of a sweep sets the time and the pairs kernel takes all (n <=
-// 256; us per backward, other kernel / pairs, tau = 1e-3: 8 heads GQA 4:1 D = 128, n = 16
-// (1024 tokens) 211 / 117, n = 64 (4096 tokens) 729 / 395, n = 256 (4 x 4096) 797 / 760; 2 x
-// 4 heads x 700 tokens 104 / 69; MHA 8 heads x 4096, D = 64, n = 256 265 / 251).  Above,
-// where every tile is retained the other kernel is ahead (n = 512: 463 / 564, n = 1024: 1194
-// / 1541), so the pairs take sequences that skip, which a tolerance below 0.1 does not
-// promise.  Both kernels are then launched and one of them leaves at once, at ~1.2 us per
-// workgroup: under 2% of sweeps of 512 iterations and more.  8 x 4096 language-model-like
-// tokens at tau = 1: 872 / 522.
 template <int D>
 static void launch_bwd_t(BwdParams p, hipStream_t st) {
   dim3 grid_q((unsigned)p.nqblk * p.B * p.Hq), block_q(kDqWaves * 64);
   const unsigned n = (unsigned)p.nkblk * p.B * p.Hkv * p.nparts;   // 128-key sweeps
   const DkdvRule rule = dkdv_rule(p);
-  p.by_sequence = rule == DkdvRule::kBySequence;
   // the dQ pass first: it records the tile decisions that the key-major pass follows
   // (dQ pass, us per backward, other kernel / rows kernel, D = 128 GQA 8/2 unless stated: 128
   // tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,
@@ -1603,10 +1677,14 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
   }
   if (rule == DkdvRule::kBlocks)
     hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, false>), dim3(n), dim3(1024), 0, st, p);
-  if (rule == DkdvRule::kBySequence)
-    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n), dim3(1024), 0, st, p);
-  if (rule != DkdvRule::kBlocks)
+  if (rule == DkdvRule::kPairs)
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_kernel<D>, dim3(4 * n), dim3(512), 0, st, p);
+  if (rule == DkdvRule::kBySequence) {
+    hipLaunchKernelGGL(mala_bwd_choose_kernel, dim3((unsigned)p.B), dim3(512), 0, st, p);
+    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n), dim3(1024), 0, st, p);
+    hipLaunchKernelGGL(mala_bwd_dkdv_pairs_sparse_kernel<D>,
+                       dim3(std::min(4 * n, kPairsSparseGrid)), dim3(512), 0, st, p);
+  }
   if (p.nparts > 1) {
     const long slices = (long)p.B * p.Hkv, blocks = ((long)p.max_len_k * (D / 4) + 255) / 256;
     hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<D>,

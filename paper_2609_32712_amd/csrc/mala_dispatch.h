@@ -66,8 +66,18 @@ inline void dkdv_split_packed(int num_seqs, int max_q, int total_k, int Hq, int 
   *nparts = (int)((longest + ps - 1) / ps);
 }
 
-// The dK/dV kernels of a call: pairs (all sweeps), blocks (all sweeps), or each sequence by
-// the tiles that the dQ pass retained.
+// The dK/dV kernel of a call.  n: sweeps of 128-key blocks (or their parts).  Where they
+// leave CUs idle the chain of a sweep sets the time and the pairs kernel takes all (n <=
+// 256; us per backward, other kernel / pairs, tau = 1e-3: 8 heads GQA 4:1 D = 128, n = 16
+// (1024 tokens) 211 / 117, n = 64 (4096 tokens) 729 / 395, n = 256 (4 x 4096) 797 / 760; 2 x
+// 4 heads x 700 tokens 104 / 69; MHA 8 heads x 4096, D = 64, n = 256 265 / 251).  Above,
+// where every tile is retained the other kernel is ahead (n = 512: 463 / 564, n = 1024: 1194
+// / 1541), so the pairs take sequences that skip, which a tolerance below 0.1 does not
+// promise.  mala_bwd_choose_kernel then marks them, both kernels are launched and each skips
+// the other's sequences, for ~20 us in all where none is sparse (a backward of 8 x 4096
+// tokens, GQA 8/2, whose sweeps are the shortest that take this way: D = 128 838 / 848, D = 64
+// 810 / 832; 16384 tokens, D = 64: 1992 / 2047).  Language-model-like tokens at tau = 1, D =
+// 128: 8 x 4096 850 / 530, 32768 4478 / 3168.
 enum class DkdvRule { kPairs, kBlocks, kBySequence };
 constexpr long kPairsGridMax = 16384;        // 128-key sweeps, four workgroups each
 

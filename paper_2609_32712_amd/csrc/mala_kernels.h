@@ -155,9 +155,6 @@ struct BwdParams {
   int psize, nparts;
   float* part;
   size_t part_rows;
-  // Both dK/dV kernels are launched and each sequence goes by its decisions: to the pairs
-  // kernel when it is sparse (sparse_sequence), else to the other one.
-  int by_sequence;
 };
 
 // Byte of the decisions of query-tile row `row` (mask_row0 + query tile), query head
@@ -173,46 +170,11 @@ __device__ __forceinline__ int mask_row0(const BwdParams& p, int b, const Seg& s
   return p.cu ? (int)(sg.qb / kBq) + b : b * ((p.Nq + kBq - 1) / kBq);
 }
 
-// Whether sequence b (nqt query tiles, off = keys - queries) retains few tiles per step of
-// 128 keys: the pairs kernel takes ~0.5 us per retained tile and key group (two per ~1 us
-// step), the other ~1.14 us per step that any of the four groups takes part in, so the
-// pairs are ahead below ~2.2 tiles per step; the line at 1.65 leaves room for their four
-// times as many list scans and tile loads (backward, other kernel / pairs: 32768 tokens,
-// GQA 8/2, 1.58 tiles per step 4.7 / 3.7 ms; 131072 tokens, 1.74: 69.3 / 72.0 ms).  Judged
-// on 2048 bytes of the dQ pass's decisions, spread over the sequence's query tiles, heads
-// and key blocks and weighted by a tile's legal blocks: the same bytes, hence the same
-// answer, in every workgroup of both kernels.  NT threads, all of which call it; red holds
-// NT / 64 pairs.
-template <int NT>
-__device__ __forceinline__ bool sparse_sequence(const BwdParams& p, int nqt, long off, int row0,
-                                                longlong2* red) {
-  long n_tiles = 0, n_steps = 0;
-#pragma unroll
-  for (int u = 0; u < 2048 / NT; ++u) {
-    const uint32_t i = threadIdx.x + NT * u;
-    const uint32_t r = i * 2654435769u;            // Fibonacci hashing: blocks and heads
-    const int qt = (int)((long)nqt * i >> 11);
-    const int nb = (int)(((long)qt * kBq + off) / kBwdKeys) + 1;   // blocks row qt kBq sees
-    const int jb = (int)((uint64_t)(r & 0xffff) * nb >> 16);
-    const int dec = p.mask[mask_index(p, row0 + qt, (int)((r >> 16) % (uint32_t)p.Hq), jb)];
-    n_tiles += (long)__popc(dec) * nb;
-    n_steps += dec ? nb : 0;
-  }
-#pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) {
-    n_tiles += __shfl_xor(n_tiles, w);
-    n_steps += __shfl_xor(n_steps, w);
-  }
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = longlong2{n_tiles, n_steps};
-  __syncthreads();
-  n_tiles = n_steps = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    n_tiles += red[w].x;
-    n_steps += red[w].y;
-  }
-  __syncthreads();   // red may be the caller's other shared memory
-  return 100 * n_tiles < 165 * n_steps;
+// Decision byte of a sequence (its query-tile row row0) whose top bit mala_bwd_choose_kernel
+// sets for the pairs kernel: that of its first query tile, head 0 and key block 0.
+constexpr int kSparseBit = 0x80;
+__device__ __forceinline__ bool sequence_is_sparse(const BwdParams& p, int row0) {
+  return p.mask[mask_index(p, row0, 0, 0)] & kSparseBit;
 }
 
 struct DecParams {

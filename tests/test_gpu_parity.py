@@ -1134,6 +1134,31 @@ def test_small_and_large_grid_backwards_give_the_same_bits(B, Hq, Hkv, N, D, tau
     _check_backward_passes_agree(cb)
 
 
+def test_backward_by_sequence_gives_the_same_bits():
+    # tau = 1, long sweeps, more than 256 of them: each sequence goes by its decisions, the
+    # sparse one (language-model-like) to the kernel of query-tile pairs, whose workgroups
+    # then take several of the call's 8192 items, the diffuse one to the kernel of 128-key
+    # blocks.  A single head is one call of pairs.  Two streams of decisions, the same bits.
+    H, N, D, tau = 8, 16384, 128, 1.0
+    w = [Workload(dict(kind="train", B=1, Hq=H, Hkv=H, N=N, D=D, **a)) for a in (
+        dict(beta=2.0, local=2.0, needle_block=32, sink=1.5), dict(beta=0.3))]
+    t = [x.tensors() for x in w]
+    q, k, v, do = (torch.cat([dev(x[n]) for x in t]) for n in ("q", "k", "v", "do"))
+    s = f32(w[0].scale)
+    f = mala.fwd(q, k, v, s, tau)
+    b = mala.bwd(q, k, v, f["o"], f["lse"], do, s, tau)
+    for i, sparse in ((0, True), (1, False)):
+        for h in (0, H - 1):
+            one = [x[i:i + 1, h:h + 1].contiguous() for x in (q, k, v, f["o"], f["lse"], do)]
+            c = mala.bwd(*one, s, tau)
+            torch.cuda.synchronize()
+            cnt = counters(c["counters"])
+            assert (cnt[mala.CNT_RETAINED] < 1.65 * cnt[mala.CNT_V_TILES]) == sparse
+            for n in ("dq", "dk", "dv"):
+                assert torch.equal(c[n][0, 0], b[n][i, h]), (i, h, n)
+    _check_backward_passes_agree(counters(b["counters"]))
+
+
 def test_concurrent_streams_match_sequential():
     # the library keeps no device state between calls: two forward + backward calls
     # on two streams at once give the results of the calls run one after the other
