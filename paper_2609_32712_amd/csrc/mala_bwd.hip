@@ -29,7 +29,7 @@
 // tiles into LDS; role 2 forms dP and dS; role 3 accumulates dK two tiles later (dS
 // handed on as bf16 operands).
 // mala_bwd_dkdv_pairs_kernel does the same for 32 keys per workgroup and two query tiles
-// per step, for grids of few key blocks and sequences that retain few tiles (dkdv_rule).
+// per step, for grids of few key blocks and sequences that retain few tiles (dkdv_plan).
 // On small grids the sweeps run in parts whose sums mala_bwd_dkdv_reduce_kernel
 // adds.  An MFMA with its operands exchanged gives the transposed scores bit for
 // bit, so both kernels see the same scores.
@@ -1657,7 +1657,7 @@ template <int D>
 static void launch_bwd_t(BwdParams p, hipStream_t st) {
   dim3 grid_q((unsigned)p.nqblk * p.B * p.Hq), block_q(kDqWaves * 64);
   const unsigned n = (unsigned)p.nkblk * p.B * p.Hkv * p.nparts;   // 128-key sweeps
-  const DkdvRule rule = dkdv_rule(p);
+  const DkdvRule rule = dkdv_plan(p, D).rule;
   // the dQ pass first: it records the tile decisions that the key-major pass follows
   // (dQ pass, us per backward, other kernel / rows kernel, D = 128 GQA 8/2 unless stated: 128
   // tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,

@@ -66,30 +66,74 @@ inline void dkdv_split_packed(int num_seqs, int max_q, int total_k, int Hq, int 
   *nparts = (int)((longest + ps - 1) / ps);
 }
 
-// The dK/dV kernel of a call.  n: sweeps of 128-key blocks (or their parts).  Where they
-// leave CUs idle the chain of a sweep sets the time and the pairs kernel takes all (n <=
-// 256; us per backward, other kernel / pairs, tau = 1e-3: 8 heads GQA 4:1 D = 128, n = 16
-// (1024 tokens) 211 / 117, n = 64 (4096 tokens) 729 / 395, n = 256 (4 x 4096) 797 / 760; 2 x
-// 4 heads x 700 tokens 104 / 69; MHA 8 heads x 4096, D = 64, n = 256 265 / 251).  Above,
-// where every tile is retained the other kernel is ahead (n = 512: 463 / 564, n = 1024: 1194
-// / 1541), so the pairs take sequences that skip, which a tolerance below 0.1 does not
-// promise.  mala_bwd_choose_kernel then marks them, both kernels are launched and each skips
-// the other's sequences, for ~20 us in all where none is sparse (a backward of 8 x 4096
-// tokens, GQA 8/2, whose sweeps are the shortest that take this way: D = 128 838 / 848, D = 64
-// 810 / 832; 16384 tokens, D = 64: 1992 / 2047).  Language-model-like tokens at tau = 1, D =
-// 128: 8 x 4096 850 / 530, 32768 4478 / 3168.
-enum class DkdvRule { kPairs, kBlocks, kBySequence };
-constexpr long kPairsGridMax = 16384;        // 128-key sweeps, four workgroups each
+// Time (us) of a dK/dV pass over n sweeps of `total` iterations in all, the longest of
+// `longest`: the pairs kernel takes ~0.5 us per iteration and tile of 32 keys, four items per
+// 128 keys, the blocks kernel ~1.14 us, each some iterations more per item, and a CU holds
+// one item at a time.  It is the longest sweep's chain where CUs are idle, else the chip's
+// share of all of them, in whole rounds where the sweeps are few and alike.
+inline double dkdv_time(bool pairs, double n, double total, double longest) {
+  const double items = pairs ? 4 * n : n, us = pairs ? 0.5 : 1.14, more = pairs ? 6 : 8;
+  const double chain = (longest + more) * us;
+  double t = std::max(chain, items / kNumCus * (total / n + more) * us);
+  if (total >= 0.7 * n * longest && items < 3 * kNumCus)
+    t = std::max(t, std::ceil(items / kNumCus) * chain);
+  return t;
+}
 
+// The dK/dV kernels of a call: pairs (all sweeps), blocks (all sweeps), or each sequence by
+// the tiles that the dQ pass retained.
+enum class DkdvRule { kPairs, kBlocks, kBySequence };
+struct DkdvPlan {
+  DkdvRule rule;
+};
+constexpr long kPairsGridMax = 16384;        // 128-key sweeps, four workgroups each
+constexpr long kPairsSweeps = 272;           // ~4 items of pairs per CU
+
+// The kernel of the sweeps where every tile is retained is the one that dkdv_time finds ahead
+// (us per backward, blocks / pairs, tau = 1e-3, D = 128 unless stated; n sweeps: 8 heads GQA
+// 4:1, n = 16 (1024 tokens) 211 / 117, n = 64 (4096 tokens) 729 / 395, n = 256 (4 x 4096) 779 /
+// 715; 16 x 2048, 16 heads, n = 256, 156 / 152; 32 heads x 1024, n = 256, 103 / 105; against
+// more keys than queries, whose sweeps are alike: 512 rows x 4096 keys, 32/8 heads, n = 256,
+// 181 / 227; 2 x 2048 x 8192, 8/2 heads, n = 256, 571 / 750; 256 x 2048, 32/8 heads, n = 128,
+// 76 / 70; 8192 tokens, 8/1 heads, 160 parts, 903 / 985).  With n = 512 blocks are always
+// ahead (463 / 564).
+//
+// Sequences that skip are the pairs' in any case (tau = 1, language-model-like, D = 128: 32
+// heads x 1024 87 / 75, 512 x 4096 rows 188 / 144), but a tolerance below 0.1 does not promise
+// that they do.  mala_bwd_choose_kernel marks them, both kernels are launched and each skips
+// the other's sequences, for ~20 us in all where none is sparse (a backward of 8 x 4096
+// tokens, GQA 8/2: D = 128 838 / 848, D = 64 810 / 832; 16384 tokens, D = 64: 1992 / 2047).
+// Language-model-like tokens at tau = 1, D = 128: 8 x 4096 850 / 530, 32768 4478 / 3168, 2 x
+// 2048 x 8192 516 / 351.
 template <class P>
-inline DkdvRule dkdv_rule(const P& p) {
+inline DkdvPlan dkdv_plan(const P& p, int D) {
   const long grid = (long)p.nkblk * p.B * p.Hkv * p.nparts;
-  if (grid > kPairsGridMax) return DkdvRule::kBlocks;   // packed batches: mostly empty workgroups
-  long n = grid;
-  if (p.cu) n = std::min(n, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
-  if (n <= kNumCus) return DkdvRule::kPairs;
-  const long longest = std::min<long>(p.psize, (long)(p.Hq / p.Hkv) * ((p.max_len + kBq - 1) / kBq));
-  return p.log2tau >= kSparseLog2Tau && longest >= 512 ? DkdvRule::kBySequence : DkdvRule::kBlocks;
+  if (grid > kPairsGridMax) return {DkdvRule::kBlocks};   // packed: mostly empty workgroups
+  const int grp = p.Hq / p.Hkv;
+  const long longest = std::min<long>(p.psize, (long)grp * ((p.max_len + kBq - 1) / kBq));
+  const bool may_skip = p.log2tau >= kSparseLog2Tau;
+  const long least = D == 128 ? 256 : 512;   // iterations that pay for the ~20 us of the choice
+  long n = 0, total = 0;
+  if (p.cu) {
+    n = std::min(grid, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
+    if (n <= kNumCus) return {DkdvRule::kPairs};
+  } else {
+    for (int j = 0; j < p.nkblk; ++j) {
+      const int its = dkdv_iterations(p.Nq, p.Nk, j * kBwdKeys, grp);
+      total += its;
+      n += (its + (long)p.psize - 1) / p.psize;
+    }
+    n *= (long)p.B * p.Hkv;
+    total *= (long)p.B * p.Hkv;
+    // sweeps too short for the choice by sequence: at D = 128 half of the tiles (94% of the
+    // blocks' iterations) is as many as any of the workloads' inputs retains
+    const double half = may_skip && D == 128 && longest < least ? 0.5 : 1.0, some = half < 1.0 ? 0.94 : 1.0;
+    if (n <= kPairsSweeps && dkdv_time(true, n, half * total, half * longest) <=
+                                 dkdv_time(false, n, some * total, some * longest))
+      return {DkdvRule::kPairs};
+  }
+  return {may_skip && longest >= (n <= kPairsSweeps ? least : 512) ? DkdvRule::kBySequence
+                                                                   : DkdvRule::kBlocks};
 }
 
 // Whether a call's time is the chain of one row block's key tiles and not the chip's

@@ -1,0 +1,95 @@
+"""The launch rules (csrc/mala_dispatch.h) on the sizes of calls, on the CPU: a small C++
+program compiled against the header answers for the shapes below."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2609_32712_amd import build as libbuild
+
+CXX = shutil.which("g++")
+pytestmark = pytest.mark.skipif(CXX is None, reason="needs g++")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "mala_dispatch.h"
+using namespace mala;
+struct P {
+  const void* cu;
+  int B, Hq, Hkv, Nq, Nk, max_len, max_len_k, nkblk, psize, nparts;
+  float log2tau;
+};
+int main() {
+  // kind (0 fixed, 1 packed), B (sequences), Hq, Hkv, Nq, Nk (totals), longest q, longest k, D, tau
+  int kind, D;
+  double tau;
+  P p;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %lf", &kind, &p.B, &p.Hq, &p.Hkv, &p.Nq, &p.Nk,
+                    &p.max_len, &p.max_len_k, &D, &tau) == 10) {
+    p.cu = kind ? &p : nullptr;
+    p.nkblk = (p.max_len_k + kBwdKeys - 1) / kBwdKeys;
+    p.log2tau = std::log2(tau);
+    if (kind)
+      dkdv_split_packed(p.B, p.max_len, p.Nk, p.Hq, p.Hkv, &p.psize, &p.nparts);
+    else
+      dkdv_split(p.B, p.Hq, p.Hkv, p.Nq, p.Nk, &p.psize, &p.nparts);
+    std::printf("%s\n", answer(p, D));
+  }
+}
+"""
+
+
+def _ask(tmp_path, answer, lines):
+    """Answers of the C++ function body `answer` (const char* from P p, int D)."""
+    src, exe = str(tmp_path / "ask.cpp"), str(tmp_path / "ask")
+    head, main = PROGRAM.split("int main")
+    with open(src, "w") as f:
+        f.write(head + "const char* answer(const P& p, int D) {\n" + answer + "}\nint main" + main)
+    subprocess.run([CXX, "-std=c++17", "-Wall", "-Werror", "-I" + libbuild.CSRC, src, "-o", exe],
+                   check=True)
+    text = "\n".join(" ".join(map(str, x)) for x in lines)
+    return subprocess.run([exe], input=text, check=True, capture_output=True, text=True).stdout.split()
+
+
+def _fixed(B, Hq, Hkv, Nq, Nk, D, tau):
+    return (0, B, Hq, Hkv, Nq, Nk, Nq, Nk, D, tau)
+
+
+DKDV = """  switch (dkdv_plan(p, D).rule) {
+    case DkdvRule::kPairs: return "pairs";
+    case DkdvRule::kBlocks: return "blocks";
+    case DkdvRule::kBySequence: return "sequence";
+  }
+  return "";
+"""
+
+
+def test_dkdv_kernel_of_fixed_length_calls(tmp_path):
+    # the faster kernel by measurement (backwards at tau = 1e-3, all tiles retained)
+    want = {(1, 8, 2, 1024, 1024): "pairs", (1, 8, 2, 4096, 4096): "pairs",
+            (4, 8, 2, 4096, 4096): "pairs", (16, 8, 2, 700, 700): "pairs",
+            (1, 8, 8, 4096, 4096): "pairs", (1, 32, 8, 1024, 1024): "pairs",
+            (1, 32, 8, 256, 2048): "pairs", (1, 8, 1, 4096, 4096): "pairs",
+            (8, 8, 2, 4096, 4096): "blocks", (1, 8, 2, 131072, 131072): "blocks",
+            # sweeps alike: the pairs' work and not the chain of one sweep sets the time
+            (2, 8, 2, 2048, 8192): "blocks", (8, 16, 16, 32, 256): "blocks",
+            (4, 8, 8, 64, 1024): "blocks", (1, 32, 8, 512, 4096): "blocks",
+            (2, 16, 4, 1024, 4096): "blocks", (1, 4, 4, 2048, 8192): "blocks",
+            (1, 8, 2, 512, 16384): "blocks", (1, 16, 2, 1000, 9000): "blocks",
+            (2, 4, 4, 500, 3000): "blocks", (16, 8, 8, 256, 256): "blocks",
+            (1, 32, 32, 1024, 1024): "blocks", (1, 8, 1, 8192, 8192): "blocks"}
+    got = _ask(tmp_path, DKDV, [_fixed(*x, 128, 1e-3) for x in want])
+    assert dict(zip(want, got)) == want
+    # tolerances that may skip: by sequence where the blocks kernel would have long sweeps,
+    # and at D = 128 pairs where they are short and few, but not of an iteration or two
+    skip = {(8, 8, 2, 4096, 4096): "sequence", (1, 8, 2, 131072, 131072): "sequence",
+            (2, 8, 2, 2048, 8192): "sequence", (1, 8, 2, 4096, 4096): "pairs",
+            (1, 32, 32, 1024, 1024): "pairs", (1, 32, 8, 512, 4096): "pairs",
+            (8, 16, 16, 32, 256): "blocks", (4, 8, 8, 64, 1024): "blocks",
+            (16, 8, 8, 256, 256): "blocks"}
+    got = _ask(tmp_path, DKDV, [_fixed(*x, 128, 1.0) for x in skip])
+    assert dict(zip(skip, got)) == skip
+    got = _ask(tmp_path, DKDV, [_fixed(*x, 64, 1.0) for x in want])
+    assert all(g == want[x] or g == "sequence" and x[3] * x[1] // x[2] >= 512 * 32
+               for x, g in zip(want, got))
