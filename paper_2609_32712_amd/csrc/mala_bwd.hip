@@ -285,6 +285,10 @@ __global__ __launch_bounds__(1024) void mala_bwd_dkdv_kernel(BwdParams p) {
   const int kb0 = kblk * kBwdKeys;
   if (kb0 >= Nk || Nq == 0) return;        // past the end of (or a skipped) packed sequence
   if (BYSEQ && sequence_is_sparse(p, mask_row0(p, b, sg))) return;
+  // the check's instructions shift the loops of the roles, which at D = 64 costs 2-4% (16384
+  // tokens, GQA 8/2: backward 2062 us without the check, 2159 with it); 44 bytes more bring
+  // them back to their places in 64-byte lines (2054)
+  if (BYSEQ && D == 64) asm volatile(".rept 11\n\ts_nop 0\n\t.endr");
   const long kbase = sg.kb + (long)hkv * p.Nk;   // key 0 of this (sequence, KV head)
   const int kw = kb0 + grp_k * kBk;        // first key of this wavefront's decision tile
   const int key = kw + c;                  // this lane's key (C-layout column)

@@ -101,8 +101,8 @@ constexpr long kPairsSweeps = 272;           // ~4 items of pairs per CU
 // Sequences that skip are the pairs' in any case (tau = 1, language-model-like, D = 128: 32
 // heads x 1024 87 / 75, 512 x 4096 rows 188 / 144), but a tolerance below 0.1 does not promise
 // that they do.  mala_bwd_choose_kernel marks them, both kernels are launched and each skips
-// the other's sequences, for ~20 us in all where none is sparse (a backward of 8 x 4096
-// tokens, GQA 8/2: D = 128 838 / 848, D = 64 810 / 832; 16384 tokens, D = 64: 1992 / 2047).
+// the other's sequences, for 5-20 us in all where none is sparse (a backward of 8 x 4096
+// tokens, GQA 8/2: D = 128 838 / 848, D = 64 843 / 848; 16384 tokens, D = 64: 2062 / 2054).
 // Language-model-like tokens at tau = 1, D = 128: 8 x 4096 850 / 530, 32768 4478 / 3168, 2 x
 // 2048 x 8192 516 / 351.
 template <class P>
