@@ -165,9 +165,11 @@ size_t mala_bwd_workspace_size(int B, int Hq, int Hkv, int Nq, int Nk, int D);
  * Hq (total_q / B_q + num_seqs) ceil(max_seqlen_k / 128) decision bytes, which it needs,
  * and, where the batch has fewer than 1024 key blocks (Hkv (total_q / 128 + num_seqs)) and
  * sweeps of more than 512 iterations, the fp32 dK and dV sums of the sweeps' parts as in
- * mala_bwd (P x 2 x Hkv total_q D floats).  A call whose workspace has no room for the
- * parts (P x 2 x Hkv total_k D floats) runs its sweeps whole: slower, and dK and dV then
- * differ by their sums' rounding. */
+ * mala_bwd (P x 2 x Hkv total_q D floats).  A call runs its sweeps in parts where that is
+ * faster by its sizes and the workspace has room for them (P x 2 x Hkv total_k D floats, P
+ * from the longest run of queries); otherwise whole.  dK and dV of the two differ by their
+ * sums' rounding.  With more keys than queries (cu_seqlens_k) the size returned here may not
+ * hold the parts: the sums of total_k instead of total_q keys do. */
 size_t mala_bwd_varlen_workspace_size(int num_seqs, int max_seqlen_k, int total_q, int Hq,
                                       int Hkv, int D);
 

@@ -197,11 +197,9 @@ int run_bwd(const void* q, const void* k, const void* v, const Packed& pk,
   if (!pk.cu) {
     mala::dkdv_split(B, Hq, Hkv, Nq, Nk, &p.psize, &p.nparts);
   } else {
-    // a workspace without room for the parts (e.g. sized for fewer keys), or a batch of so
-    // many sequences that most of the parts' workgroups would find none, gives whole sweeps
+    // a workspace without room for the parts (e.g. sized for fewer keys) gives whole sweeps
     mala::dkdv_split_packed(B, pk.max_q, Nk, Hq, Hkv, &p.psize, &p.nparts);
-    if (workspace_bytes < before + part_bytes_packed(B, pk.max_q, Nk, Hq, Hkv, D) ||
-        (long)p.nkblk * B * Hkv * p.nparts > 16384) {
+    if (workspace_bytes < before + part_bytes_packed(B, pk.max_q, Nk, Hq, Hkv, D)) {
       p.psize = 1 << 30;
       p.nparts = 1;
     }

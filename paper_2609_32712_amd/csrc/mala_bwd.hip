@@ -1633,12 +1633,13 @@ __global__ __launch_bounds__(512) void mala_bwd_dq_rows_kernel(BwdParams p) {
 
 // Sum of the parts of split dK/dV sweeps in part order: one thread per four columns of a
 // K-shaped row, blockIdx.y the (sequence, KV head); a row's key block has
-// ceil(iterations / psize) parts.
-template <int D>
+// ceil(iterations / psize) parts.  SPARSE: only the sparse sequences' ran in parts.
+template <int D, bool SPARSE>
 __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) {
   const int b = blockIdx.y / p.Hkv, hkv = blockIdx.y % p.Hkv, grp = p.Hq / p.Hkv;
   const Seg sg = seq_slice(p, b);
   if (sg.Nq == 0) return;   // a skipped packed sequence
+  if (SPARSE && !sequence_is_sparse(p, mask_row0(p, b, sg))) return;
   const long row0 = sg.kb + (long)hkv * p.Nk;
   const size_t slot = p.part_rows * D;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < (long)sg.Nk * (D / 4);
@@ -1660,8 +1661,10 @@ __global__ __launch_bounds__(256) void mala_bwd_dkdv_reduce_kernel(BwdParams p) 
 template <int D>
 static void launch_bwd_t(BwdParams p, hipStream_t st) {
   dim3 grid_q((unsigned)p.nqblk * p.B * p.Hq), block_q(kDqWaves * 64);
+  const DkdvPlan plan = dkdv_plan(p, D);
+  const auto whole = [](BwdParams& x) { x.psize = 1 << 30; x.nparts = 1; };
+  if (!plan.parts) whole(p);
   const unsigned n = (unsigned)p.nkblk * p.B * p.Hkv * p.nparts;   // 128-key sweeps
-  const DkdvRule rule = dkdv_plan(p, D).rule;
   // the dQ pass first: it records the tile decisions that the key-major pass follows
   // (dQ pass, us per backward, other kernel / rows kernel, D = 128 GQA 8/2 unless stated: 128
   // tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,
@@ -1679,21 +1682,26 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
       launch_preprocess<D>(static_cast<const float*>(p.o), p, rows, st);
     hipLaunchKernelGGL(mala_bwd_dq_kernel<D>, grid_q, block_q, 0, st, p);
   }
-  if (rule == DkdvRule::kBlocks)
+  if (plan.rule == DkdvRule::kBlocks)
     hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, false>), dim3(n), dim3(1024), 0, st, p);
-  if (rule == DkdvRule::kPairs)
+  if (plan.rule == DkdvRule::kPairs)
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_kernel<D>, dim3(4 * n), dim3(512), 0, st, p);
-  if (rule == DkdvRule::kBySequence) {
+  if (plan.rule == DkdvRule::kBySequence) {
     hipLaunchKernelGGL(mala_bwd_choose_kernel, dim3((unsigned)p.B), dim3(512), 0, st, p);
-    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n), dim3(1024), 0, st, p);
+    BwdParams pb = p;
+    if (!plan.block_parts) whole(pb);
+    hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n / p.nparts * pb.nparts), dim3(1024), 0,
+                       st, pb);
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_sparse_kernel<D>,
                        dim3(std::min(4 * n, kPairsSparseGrid)), dim3(512), 0, st, p);
   }
   if (p.nparts > 1) {
     const long slices = (long)p.B * p.Hkv, blocks = ((long)p.max_len_k * (D / 4) + 255) / 256;
-    hipLaunchKernelGGL(mala_bwd_dkdv_reduce_kernel<D>,
-                       dim3((unsigned)std::min(blocks, 8192 / slices + 1), (unsigned)slices),
-                       dim3(256), 0, st, p);
+    const dim3 grid((unsigned)std::min(blocks, 8192 / slices + 1), (unsigned)slices);
+    if (plan.rule == DkdvRule::kBySequence && !plan.block_parts)
+      hipLaunchKernelGGL((mala_bwd_dkdv_reduce_kernel<D, true>), grid, dim3(256), 0, st, p);
+    else
+      hipLaunchKernelGGL((mala_bwd_dkdv_reduce_kernel<D, false>), grid, dim3(256), 0, st, p);
   }
 }
 

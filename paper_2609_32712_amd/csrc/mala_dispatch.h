@@ -85,9 +85,51 @@ inline double dkdv_time(bool pairs, double n, double total, double longest) {
 enum class DkdvRule { kPairs, kBlocks, kBySequence };
 struct DkdvPlan {
   DkdvRule rule;
+  bool parts;          // the sweeps run in the call's parts (else whole),
+  bool block_parts;    // those of the blocks kernel too, where both kernels run
 };
 constexpr long kPairsGridMax = 16384;        // 128-key sweeps, four workgroups each
 constexpr long kPairsSweeps = 272;           // ~4 items of pairs per CU
+
+// Packed batches: only the device knows the lengths.  Taken as the worst of two batches
+// that the host cannot tell from others, sequences all as long as the longest, and the
+// longest alone with the rest of no length: workgroups go round the XCDs, and round their
+// shader engines, in turn, so that a sequence's have only a share of the chip (`reach`) where
+// the sequences' number has factors of two (one of 8192 tokens among 23 of 64, 2 heads, D =
+// 64: 48 slices, 1 / 8 of the chip; backward by blocks / pairs 857 / 1219 us).  Parts help
+// where neither batch fills the chip without them (8192 + 4096 + 2048 + 1024 + 512 tokens, 8/2
+// heads, D = 128: whole 1389 us, parts 1020) and cost the partial sums where one does (2 x 8192,
+// 16/4 heads: 2083 / 2194).  Where the sequences go by their decisions, the pairs' sweeps,
+// most of all an attention sink's, are uneven, and run in parts in any case (a sequence of
+// 16384 among eight shorter ones, 8/2 heads, language-model-like: 1591 / 1221).
+template <class P>
+inline DkdvPlan dkdv_plan_packed(const P& p, int D) {
+  const int grp = p.Hq / p.Hkv, slices = p.B * p.Hkv;
+  const double grid = (double)p.nkblk * slices, longest = (double)grp * ((p.max_len + kBq - 1) / kBq);
+  if (grid > kPairsGridMax) return {DkdvRule::kBlocks, false, false};   // mostly empty workgroups
+  const double n = std::min(grid, (double)p.Hkv * (p.Nk / kBwdKeys + p.B));
+  const double reach = std::min(1.0, (double)p.Hkv / std::gcd(slices, 32));
+  const double sweeps = std::max(n, p.Hkv * p.nkblk / reach), total = sweeps * longest / 2;
+  const double empty = (grid - n) / kNumCus * 1.2;                      // us, per workgroup and sweep
+  const bool may_skip = p.log2tau >= kSparseLog2Tau;
+  const double half = may_skip && D == 128 && longest < 512 ? 0.5 : 1.0;   // as for fixed lengths
+  double best = dkdv_time(false, sweeps, total, longest) + empty;
+  double pairs = dkdv_time(true, sweeps, half * total, half * longest) + 4 * empty;
+  bool pair_parts = false, block_parts = false;
+  const bool can_split = p.nparts > 1 && grid * p.nparts <= kPairsGridMax;
+  if (can_split) {
+    const double parts = total / p.psize + sweeps / 2, more = (p.nparts - 1) * grid / kNumCus * 1.2;
+    const double pp = 1.05 * dkdv_time(true, parts, total, p.psize) + 4 * (empty + more);
+    const double bp = 1.05 * dkdv_time(false, parts, total, p.psize) + empty + more + 20;
+    pair_parts = may_skip || pp < pairs;
+    pairs = std::min(pairs, pp);
+    block_parts = bp < 0.9 * best;
+    if (block_parts) best = bp;
+  }
+  if (pairs < 0.9 * best) return {DkdvRule::kPairs, pair_parts, false};
+  if (may_skip && longest >= 512) return {DkdvRule::kBySequence, can_split, block_parts};
+  return {DkdvRule::kBlocks, block_parts, block_parts};
+}
 
 // The kernel of the sweeps where every tile is retained is the one that dkdv_time finds ahead
 // (us per backward, blocks / pairs, tau = 1e-3, D = 128 unless stated; n sweeps: 8 heads GQA
@@ -107,33 +149,29 @@ constexpr long kPairsSweeps = 272;           // ~4 items of pairs per CU
 // 2048 x 8192 516 / 351.
 template <class P>
 inline DkdvPlan dkdv_plan(const P& p, int D) {
-  const long grid = (long)p.nkblk * p.B * p.Hkv * p.nparts;
-  if (grid > kPairsGridMax) return {DkdvRule::kBlocks};   // packed: mostly empty workgroups
+  if (p.cu) return dkdv_plan_packed(p, D);
+  const bool parts = p.nparts > 1;
+  if ((long)p.nkblk * p.B * p.Hkv * p.nparts > kPairsGridMax) return {DkdvRule::kBlocks, parts, parts};
   const int grp = p.Hq / p.Hkv;
   const long longest = std::min<long>(p.psize, (long)grp * ((p.max_len + kBq - 1) / kBq));
   const bool may_skip = p.log2tau >= kSparseLog2Tau;
   const long least = D == 128 ? 256 : 512;   // iterations that pay for the ~20 us of the choice
   long n = 0, total = 0;
-  if (p.cu) {
-    n = std::min(grid, (long)p.Hkv * (p.Nk / kBwdKeys + p.B) * p.nparts);
-    if (n <= kNumCus) return {DkdvRule::kPairs};
-  } else {
-    for (int j = 0; j < p.nkblk; ++j) {
-      const int its = dkdv_iterations(p.Nq, p.Nk, j * kBwdKeys, grp);
-      total += its;
-      n += (its + (long)p.psize - 1) / p.psize;
-    }
-    n *= (long)p.B * p.Hkv;
-    total *= (long)p.B * p.Hkv;
-    // sweeps too short for the choice by sequence: at D = 128 half of the tiles (94% of the
-    // blocks' iterations) is as many as any of the workloads' inputs retains
-    const double half = may_skip && D == 128 && longest < least ? 0.5 : 1.0, some = half < 1.0 ? 0.94 : 1.0;
-    if (n <= kPairsSweeps && dkdv_time(true, n, half * total, half * longest) <=
-                                 dkdv_time(false, n, some * total, some * longest))
-      return {DkdvRule::kPairs};
+  for (int j = 0; j < p.nkblk; ++j) {
+    const int its = dkdv_iterations(p.Nq, p.Nk, j * kBwdKeys, grp);
+    total += its;
+    n += (its + (long)p.psize - 1) / p.psize;
   }
+  n *= (long)p.B * p.Hkv;
+  total *= (long)p.B * p.Hkv;
+  // sweeps too short for the choice by sequence: at D = 128 half of the tiles (94% of the
+  // blocks' iterations) is as many as any of the workloads' inputs retains
+  const double half = may_skip && D == 128 && longest < least ? 0.5 : 1.0, some = half < 1.0 ? 0.94 : 1.0;
+  if (n <= kPairsSweeps && dkdv_time(true, n, half * total, half * longest) <=
+                               dkdv_time(false, n, some * total, some * longest))
+    return {DkdvRule::kPairs, parts, false};
   return {may_skip && longest >= (n <= kPairsSweeps ? least : 512) ? DkdvRule::kBySequence
-                                                                   : DkdvRule::kBlocks};
+                                                                   : DkdvRule::kBlocks, parts, parts};
 }
 
 // Whether a call's time is the chain of one row block's key tiles and not the chip's

@@ -93,3 +93,49 @@ def test_dkdv_kernel_of_fixed_length_calls(tmp_path):
     got = _ask(tmp_path, DKDV, [_fixed(*x, 64, 1.0) for x in want])
     assert all(g == want[x] or g == "sequence" and x[3] * x[1] // x[2] >= 512 * 32
                for x, g in zip(want, got))
+
+
+def _packed(lens, Hq, Hkv, D, tau):
+    return (1, len(lens), Hq, Hkv, sum(lens), sum(lens), max(lens), max(lens), D, tau)
+
+
+PACKED = """  static char s[64];
+  const DkdvPlan q = dkdv_plan(p, D);
+  std::snprintf(s, sizeof(s), "%s%s%s",
+                q.rule == DkdvRule::kPairs ? "pairs" : q.rule == DkdvRule::kBlocks ? "blocks" : "sequence",
+                q.parts ? "+parts" : "", q.rule == DkdvRule::kBySequence && q.block_parts ? "+both" : "");
+  return s;
+"""
+
+
+def test_dkdv_plan_of_packed_batches(tmp_path):
+    # the faster plan by measurement (backwards at tau = 1e-3); unless stated, another kernel
+    # or the other choice of parts took 5-40% longer
+    one_long, rest = [8192] + [64] * 23, [8192, 1000, 1000, 1000]
+    want = [
+        # the longest sequence's workgroups fall to a share of the chip: pairs' work and the
+        # parts' sums make it worse
+        (_packed(one_long, 2, 2, 64, 1e-3), "blocks"), (_packed(one_long, 4, 1, 128, 1e-3), "blocks"),
+        (_packed([16384, 64, 64, 64], 8, 1, 64, 1e-3), "blocks"),
+        (_packed(rest, 2, 2, 128, 1e-3), "blocks"), (_packed(rest, 8, 2, 128, 1e-3), "blocks"),
+        # equal sequences fill the chip whole
+        (_packed([8192] * 2, 16, 4, 128, 1e-3), "blocks"), (_packed([16384] * 2, 8, 2, 128, 1e-3), "blocks"),
+        (_packed([9000] * 7, 8, 1, 128, 1e-3), "blocks"), (_packed([6000] * 5, 16, 2, 128, 1e-3), "blocks"),
+        (_packed([8192, 100], 32, 8, 128, 1e-3), "blocks"),
+        (_packed([6000, 3000, 1500, 700, 350], 32, 8, 64, 1e-3), "blocks"),
+        (_packed([130] * 16, 32, 8, 64, 1e-3), "blocks"),    # a tie
+        # few blocks: parts, or pairs
+        (_packed([8192, 4096, 2048, 1024, 512], 8, 2, 128, 1e-3), "blocks+parts"),
+        (_packed([6000, 3000, 1500, 700, 350], 16, 4, 128, 1e-3), "blocks+parts"),
+        (_packed([16384, 8192, 4096, 1500, 1024, 1000, 500, 68, 4], 4, 1, 128, 1e-3), "blocks+parts"),
+        (_packed([9000] * 5, 8, 1, 128, 1e-3), "blocks+parts"),
+        (_packed([8192, 4096, 2048, 1024, 512], 4, 1, 128, 1e-3), "pairs"),
+        (_packed([6000, 3000, 1500, 700, 350], 4, 1, 128, 1e-3), "pairs+parts"),
+        (_packed([3000] + [700] * 9, 2, 2, 64, 1e-3), "pairs"),
+        # by sequence: the sparse ones in parts, the others by the same rule as above
+        (_packed([16384, 8192, 4096, 1500, 1024, 1000, 500, 68, 4], 8, 2, 128, 1.0), "sequence+parts"),
+        (_packed([6000, 3000, 1500, 700, 350], 16, 4, 128, 1.0), "sequence+parts+both"),
+        (_packed([16384] * 4, 32, 8, 128, 1.0), "sequence"),
+        (_packed([8192, 100], 4, 1, 128, 1.0), "pairs+parts")]
+    got = _ask(tmp_path, PACKED, [x for x, _ in want])
+    assert got == [a for _, a in want]

@@ -413,6 +413,51 @@ def test_varlen_full_size_equals_per_sequence_calls(tau):
                 assert torch.equal(a[:, r], ref[0]), (b, name)
 
 
+@pytest.mark.parametrize("more_keys", [0, 2500])
+@pytest.mark.parametrize("tau", [1e-3, 1.0])
+def test_varlen_backward_workspaces(tau, more_keys):
+    # A packed backward accepts D_q and the decision bytes alone (whole sweeps) and runs its
+    # sweeps in parts where the workspace has room for them: the queried size does when keys
+    # and queries are as many, with more keys only a larger buffer.  Nothing is written past
+    # any of them; dQ is the same, dK and dV agree within the sum of both paths' lo-term
+    # bounds (2^-8 x budget x the largest |dO| or scale |Q|: 2e-3 for these inputs).
+    lens, Hq, Hkv, D = [8192, 512, 512], 8, 2, 128
+    w = Workload(dict(kind="train", B=1, Hq=Hq, Hkv=Hkv, N=sum(lens) + more_keys * len(lens), D=D,
+                      beta=2.0, local=1.0))
+    t = w.tensors()
+    total, S = sum(lens), len(lens)
+    cu = [sum(lens[:i]) for i in range(S + 1)]
+    cuk = [c + more_keys * i for i, c in enumerate(cu)]
+    q, do = (dev(np.ascontiguousarray(t[x][0, :, :total])) for x in ("q", "do"))
+    k, v = (dev(t[x][0]) for x in ("k", "v"))
+    CU, CUK = (torch.tensor(x, dtype=torch.int32, device="cuda") for x in (cu, cuk))
+    kw = dict(cu_seqlens_k=CUK, max_seqlen_k=lens[0] + more_keys) if more_keys else {}
+    mk = lens[0] + more_keys
+    s = f32(w.scale)
+    f = mala.fwd_varlen(q, k, v, CU, lens[0], s, tau, **kw)
+    up = lambda n: (n + 255) // 256 * 256
+    least = up(Hq * total * 4) + up(Hq * -(-mk // 128) * (total // 32 + S))
+    asked = mala.mala_bwd_varlen_workspace_size(S, mk, total, Hq, Hkv, D)
+    assert asked > least
+    full = least + (asked - least) * k.shape[1] // total + 256
+    out = {}
+    for name, n in (("least", least), ("asked", asked), ("full", full)):
+        buf = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        out[name] = mala.bwd_varlen(q, k, v, CU, lens[0], f["o"], f["lse"], do, s, tau,
+                                    workspace=buf[:n], **kw)
+        torch.cuda.synchronize()
+        assert (buf[n:] == 0xA5).all(), name
+    for x in out.values():
+        assert torch.equal(x["dq"], out["least"]["dq"])
+        for n in ("dk", "dv"):
+            assert (x[n] - out["least"][n]).abs().max().item() <= 2e-3, n
+    whole = [torch.equal(out[x]["dk"], out["least"]["dk"]) for x in ("asked", "full")]
+    assert whole == [more_keys > 0, False]
+    with pytest.raises(mala.MalaError):
+        mala.bwd_varlen(q, k, v, CU, lens[0], f["o"], f["lse"], do, s, tau,
+                        workspace=torch.empty(least - 1, dtype=torch.uint8, device="cuda"), **kw)
+
+
 DECODE_CASES = [
     (dict(kind="decode", B=2, Hq=8, Hkv=2, N=3001, D=128, beta=3.0, needles=4), 1, 0.0),
     (dict(kind="decode", B=2, Hq=8, Hkv=2, N=3001, D=128, beta=3.0, needles=4), 4, 1e-4),
