@@ -91,7 +91,7 @@ def _check_backward_passes_agree(cb):
     # equal retained counts and equal fingerprints of the retained tile sets
     assert cb[mala.CNT_RETAINED_KV] == cb[mala.CNT_RETAINED], cb
     assert cb[mala.CNT_SET_HASH_KV] == cb[mala.CNT_SET_HASH], cb
-    # the key-major pass loads a dO tile only for the query tiles it processes
+    # the key-major pass needs a dO tile only for the query tiles it processes
     assert cb[mala.CNT_V_NEEDED] == cb[mala.CNT_V_TILES] >= 0, cb
 
 
@@ -380,10 +380,10 @@ def test_varlen_full_size_equals_per_sequence_calls(tau):
     # 32768 packed tokens of the language-model-like inputs: every sequence's
     # outputs equal, bit for bit, a fixed-length call on that sequence alone (the
     # same tiles from the sequence's first row, the same arithmetic).  Except dK and
-    # dV where the fixed-length call splits its key-block sweeps (few key-block
-    # workgroups): its parts add their sums afterwards and share the lo-term budgets,
-    # so the two agree within the sum of their error bounds (2^-8 x budget x the
-    # largest |dO| or scale |Q|, per path)
+    # dV where either call splits the sequence's key-block sweeps (the packed one, from
+    # its own sizes, where the fixed-length one does, if at all): parts add their sums
+    # afterwards and share the lo-term budgets, so the two agree within the sum of their
+    # error bounds (2^-8 x budget x the largest |dO| or scale |Q|, per path)
     lens = [16384, 8192, 4096, 1500, 1024, 1000, 500, 68, 4]
     w, cu, t = _packed(dict(WORKLOADS["lm_like_gqa8x2_32k"], B=1), lens)
     scale = f32(w.scale)
@@ -523,55 +523,72 @@ VARLEN_DECODE_CASES = [
      0.1),
     (dict(kind="decode", B=4, Hq=16, Hkv=1, N=2048, D=128, beta=2.0, needles=2),
      [2048, 1000, 31, 1500], 7, 1.0),
+    (dict(kind="decode", B=4, Hq=8, Hkv=2, N=1000, D=64, beta=3.0, needles=4), [0, 1000, 1, 65],
+     3, 1e-3),
 ]
 
 
+def _copies_beyond_teams(w, splits):
+    """Copies of a decode batch whose splits are more than the 256 that teams of wavefronts
+    take: they run on one wavefront each."""
+    return 256 // (w.B * w.Hkv * -(-w.Hq // w.Hkv // 16) * splits) + 1
+
+
 @pytest.mark.parametrize("spec,lens,splits,tau", VARLEN_DECODE_CASES)
-def test_decode_per_sequence_cache_lengths(spec, lens, splits, tau):
-    # each sequence against the oracle on its own valid prefix of the cache
+@pytest.mark.parametrize("many", [False, True])
+def test_decode_per_sequence_cache_lengths(spec, lens, splits, tau, many):
+    # each sequence against the oracle on its own valid prefix of the cache; many: copies of
+    # the batch, so that each split is one wavefront's
     w = Workload(spec)
     t = w.tensors()
     scale = f32(w.scale)
     bk = mala.mala_geometry(w.D, mala.PASS_DECODE)[1]
     qf, kf, vf = map(bf16_to_f64, (t["q"], t["k"], t["v"]))
-    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
-    g = mala.decode(dev(t["q"]), dev(t["k"]), dev(t["v"]), scale, tau, splits, cache_lens=cl)
+    copies = _copies_beyond_teams(w, splits) if many else 1
+    cl = torch.tensor(lens * copies, dtype=torch.int32, device="cuda")
+    x = [dev(t[n]).repeat(copies, *[1] * (t[n].ndim - 1)) for n in ("q", "k", "v")]
+    g = mala.decode(*x, scale, tau, splits, cache_lens=cl)
     torch.cuda.synchronize()
     o, lse, ht = host(g["o"]), host(g["lse"]), host(g["head_tiles"])
     legal, keeps, exs = 0, [], []
     for b, n in enumerate(lens):
         n = min(max(n, 0), w.N)
+        same = range(b, w.B * copies, w.B)
         if n == 0:
-            assert (o[b] == 0).all() and np.isneginf(lse[b]).all() and (ht[b] == 0).all()
+            assert (o[same] == 0).all() and np.isneginf(lse[same]).all() and (ht[same] == 0).all()
             continue
         od = oracle.mala_decode(qf[b:b + 1], kf[b:b + 1, :, :n], vf[b:b + 1, :, :n], scale,
                                 f32(tau), bk, splits, want_tiles=True)
-        assert_close("decode O seq %d (n=%d)" % (b, n), o[b], od["o"][0])
-        assert np.abs(lse[b] - od["lse"][0]).max() <= LSE_DIAG
-        exs.append(assert_counts("decode head tiles seq %d" % b, ht[b:b + 1], od["tiles"], tau,
-                                 ties(od)).any())
-        keeps.append((b, od["keep"]))
-        legal += -(-n // bk) * w.Hq
+        for i in same:
+            assert_close("decode O seq %d (n=%d)" % (i, n), o[i], od["o"][0])
+            assert np.abs(lse[i] - od["lse"][0]).max() <= LSE_DIAG
+            exs.append(assert_counts("decode head tiles seq %d" % i, ht[i:i + 1], od["tiles"],
+                                     tau, ties(od)).any())
+            keeps.append((i, od["keep"]))
+            legal += -(-n // bk) * w.Hq
     cd = counters(g["counters"])
     assert cd[mala.CNT_LEGAL] == legal
     _check_decode_counters(cd, keeps, exs, w.Hkv)
 
 
 @pytest.mark.parametrize("tau", [0.0, 1e-3])
-def test_decode_never_reads_cache_rows_past_a_length(tau):
+@pytest.mark.parametrize("D,many", [(128, False), (128, True), (64, False), (64, True)])
+def test_decode_never_reads_cache_rows_past_a_length(D, many, tau):
     # rows at and past a sequence's cache length play no part: filling them with NaN
     # leaves every output and statistic bitwise unchanged (lengths off the 32-key
     # grid, so each sequence ends in a ragged tile, and one sequence shorter than
-    # one split's share of the tiles)
-    spec = dict(kind="decode", B=3, Hq=8, Hkv=2, N=3001, D=128, beta=3.0, needles=4)
+    # one split's share of the tiles); many: copies of the batch, so that each split is one
+    # wavefront's
+    spec = dict(kind="decode", B=4, Hq=8, Hkv=2, N=3001, D=D, beta=3.0, needles=4)
     w = Workload(spec)
     t = {x: np.array(y) for x, y in w.tensors().items()}
-    lens = [3001, 1000, 37]
-    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    lens = [3001, 1000, 37, 0]
+    copies = _copies_beyond_teams(w, 4) if many else 1
+    cl = torch.tensor(lens * copies, dtype=torch.int32, device="cuda")
 
     def run():
-        g = mala.decode(dev(t["q"]), dev(t["k"]), dev(t["v"]), f32(w.scale), tau, 4,
-                        cache_lens=cl)
+        x = [dev(t[n]).repeat(copies, *[1] * (t[n].ndim - 1)) for n in ("q", "k", "v")]
+        g = mala.decode(*x, f32(w.scale), tau, 4, cache_lens=cl)
         torch.cuda.synchronize()
         return {x: y.cpu() for x, y in g.items()}
 
@@ -605,10 +622,11 @@ def test_decode_full_lengths_match_uniform_path():
 
 @pytest.mark.parametrize("Hq,Hkv,N,D,splits,tau", [
     (8, 2, 33, 128, 1, 1e-3), (4, 1, 129, 64, 1, 0.0), (40, 2, 257, 128, 2, 1.0),
-    (8, 2, 2049, 64, 2, 1e-2), (8, 2, 8191, 128, 3, 1.0), (2, 1, 1000, 128, 40, 1e-4)])
+    (8, 2, 2049, 64, 2, 1e-2), (8, 2, 8191, 128, 3, 1.0), (2, 1, 2049, 128, 40, 1e-4)])
 def test_decode_team_matches_one_wavefront_per_split(Hq, Hkv, N, D, splits, tau):
     # Up to 256 splits in a call run on teams of 4 or 8 wavefronts, more on one wavefront
-    # each: the same query and cache alone and in a batch of more than 256 splits.  The
+    # each (as do splits of a single tile): the same query and cache alone and in a batch of
+    # more than 256 splits.  The
     # sums are taken in another order (fp32, a few hundred terms: 1e-5 relative to the
     # O rows' size, ~1).
     B = 256 // (Hkv * splits) + 1
@@ -1113,6 +1131,53 @@ def test_small_grid_forward_gives_the_same_bits(B, Hq, Hkv, Nq, Nk, D):
         torch.cuda.synchronize()
         for name, x, y in (("o", a["o"], o), ("lse", a["lse"], lse), ("row_tiles", a["row_tiles"], rt)):
             assert torch.equal(x, y), (tau, name)
+
+
+# (Hq, Hkv, D, query lengths, key lengths if others, max_seqlen if less than the longest, tau):
+# a sequence shorter than a stage (128 keys), one of one token; a prefill against cached keys
+# with a sequence that is skipped (more rows than keys); sequences cut to max_seqlen
+SMALL_GRID_PACKED = [
+    (4, 2, 128, [300, 1, 64, 513, 37], None, None, 1e-3),
+    (2, 2, 64, [1000, 7, 256], None, None, 1.0),
+    (4, 2, 128, [100, 64, 1, 17, 5], [300, 64, 513, 40, 3], None, 1e-3),
+    (8, 2, 64, [100, 64, 1, 17, 5], [300, 64, 513, 40, 3], None, 0.0),
+    (2, 1, 128, [200, 150, 100], None, 140, 1e-3),
+]
+
+
+@pytest.mark.parametrize("bad", [None, "q", "k", "v"])
+@pytest.mark.parametrize("Hq,Hkv,D,lens,lens_k,cut,tau", SMALL_GRID_PACKED)
+def test_small_grid_packed_forward_gives_the_same_bits(Hq, Hkv, D, lens, lens_k, cut, tau, bad):
+    # Packed batches of few row blocks, without counters (the kernel for few row blocks) and
+    # with them: O, LSE and the row counts are the same bits, in fp32 and rounded to bf16, and
+    # what no sequence covers (rows past a cut, the last 50) stays as it was.  bad: a NaN in a
+    # row of Q or K, an Inf in one of V.
+    starts = lambda ls: np.concatenate([[0], np.cumsum(ls)])
+    cu, cuk = starts(lens), starts(lens_k or lens)
+    Nq, Nk = int(cu[-1]) + 50, int(cuk[-1]) + 50
+    w = Workload(dict(kind="train", B=1, Hq=Hq, Hkv=Hkv, N=max(Nq, Nk), D=D, beta=2.0, local=2.0))
+    t = w.tensors(with_do=False)
+    q, k, v = (np.array(t[x][0, :, :n]) for x, n in (("q", Nq), ("k", Nk), ("v", Nk)))
+    if bad:
+        {"q": q, "k": k, "v": v}[bad][0, 77, 5] = INF_BITS if bad == "v" else NAN_BITS
+    Q, K, V = dev(q), dev(k), dev(v)
+    CU, CUK = (torch.from_numpy(c.astype(np.int32)).cuda() for c in (cu, cuk))
+    kw = dict(cu_seqlens_k=CUK, max_seqlen_k=max(lens_k)) if lens_k else {}
+    out = []
+    for stats, dt in ((True, torch.float32), (False, torch.float32), (False, torch.bfloat16)):
+        o = torch.full((Hq, Nq, D), 7.0, dtype=dt, device="cuda")
+        lse = torch.full((Hq, Nq), 7.0, device="cuda")
+        rt = torch.full((Hq, Nq), -7, dtype=torch.int32, device="cuda")
+        cnt = torch.empty(mala.NUM_COUNTERS, dtype=torch.int64, device="cuda") if stats else None
+        mala.mala_fwd_varlen(Q, K, V, CU, cut or max(lens), o, lse, rt, cnt, f32(w.scale), tau, **kw)
+        torch.cuda.synchronize()
+        out.append((o.cpu(), lse.cpu(), rt.cpu()))
+    same = lambda x, y: bool(((x == y) | (x.isnan() & y.isnan())).all())
+    ref = out[0]
+    assert (ref[0][:, -50:] == 7).all() and bool(bad) == (not bool(ref[0].isfinite().all()))
+    assert same(out[1][0], ref[0]) and same(out[2][0], ref[0].to(torch.bfloat16))
+    for o, lse, rt in out[1:]:
+        assert same(lse, ref[1]) and torch.equal(rt, ref[2])
 
 
 @pytest.mark.parametrize("D", [64, 128])
