@@ -1666,11 +1666,7 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
   if (!plan.parts) whole(p);
   const unsigned n = (unsigned)p.nkblk * p.B * p.Hkv * p.nparts;   // 128-key sweeps
   // the dQ pass first: it records the tile decisions that the key-major pass follows
-  // (dQ pass, us per backward, other kernel / rows kernel, D = 128 GQA 8/2 unless stated: 128
-  // tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,
-  // 32 heads 2048 238 / 298.  At tau = 1, where the other kernel skips for less, 2048
-  // language-model-like tokens 177 / 157, 4096 331 / 339)
-  if (few_row_blocks(p, p.log2tau >= kSparseLog2Tau ? 2 : 3)) {
+  if (dq_takes_rows(p, D)) {
     const unsigned nqt = (unsigned)((p.max_len + kBq - 1) / kBq);
     hipLaunchKernelGGL(mala_bwd_dq_rows_kernel<D>, dim3(nqt * p.B * p.Hq), dim3(512), 0, st, p);
   } else {

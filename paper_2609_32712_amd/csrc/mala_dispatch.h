@@ -174,25 +174,78 @@ inline DkdvPlan dkdv_plan(const P& p, int D) {
                                                                    : DkdvRule::kBlocks, parts, parts};
 }
 
-// Whether a call's time is the chain of one row block's key tiles and not the chip's
-// throughput, so that the kernels of one workgroup per 32 query rows (the forward's and
-// the dQ pass's) are ahead of those of 256 rows.  In units of one step of the former (four
-// key tiles, ~1.1 us) its row blocks take the mean of (stages + 3) each over the CUs; the
-// chain of the latter takes `chain` such units per stage of the longest block.  Packed
-// batches hold at most total / 32 + sequences row blocks, taken as long as the longest.
-constexpr int kRowsTiles = 4;   // key tiles per stage of those kernels
+// Longest time (in the lengths' unit) that one of `cus` CUs is busy with n workgroups whose
+// lengths fall evenly from longest to shortest, the longest first, one on a CU at a time: the
+// mean share, or r rounds of which the last begins with the length of workgroup (r - 1) cus.
+inline double launch_span(double n, double shortest, double longest, double cus) {
+  const double mean = n * (shortest + longest) / 2 / cus;
+  double t = longest;
+  for (int r = 2; (r - 1) * cus < n; ++r) {
+    const double x = r * (longest - (longest - shortest) * (r - 1) * cus / n);
+    if (x <= t) break;   // rises, then falls with r
+    t = x;
+  }
+  return std::max(mean, t);
+}
+
+// Whether the kernels of one workgroup per 32 query rows (the forward's and the dQ pass's,
+// steps of four key tiles, ~3 more to fill and drain the pipeline) are ahead of those of 256
+// rows, whose chain goes tile by tile: by the span of either's workgroups over the CUs.
+// The times are fits (us: a step, a tile, what the latter kernel takes longer to start) over
+// 1600 calls of 1 to 128 heads x sequences, 96 to 4096 rows, up to 17000 keys; a tile takes
+// longer on inputs with many low terms (D = 128: 0.8-1.5 us), and the rates are near the
+// lower end, so that the choice rarely costs time.
+//
+// Packed batches, whose lengths only the device knows: ahead in both of the batches that the
+// host cannot tell from others, sequences all as long as the longest, and the longest alone
+// with the rest of no length, which has only the CUs that its (sequence, head) slices reach
+// (as for dkdv_plan_packed).  Workgroups without rows cost ~1 us of a CU each.
+constexpr int kRowsTiles = 4;   // key tiles per step of those kernels
+struct RowsRates {
+  double first, step, tile;
+};
 template <class P>
-inline bool few_row_blocks(const P& p, int chain) {
-  const long stage = kRowsTiles * kBk;
-  const long longest = (p.max_len_k + stage - 1) / stage;
-  const long grid = (long)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq;
-  long blocks = grid;
-  if (p.cu && (long)p.Hq * (p.Nq / kBq + p.B) < grid) blocks = (long)p.Hq * (p.Nq / kBq + p.B);
+inline bool rows_ahead(const P& p, const RowsRates& c) {
+  const long stage = kRowsTiles * kBk, older = p.max_len_k - p.max_len;   // keys every row sees
+  const double longest = (double)((p.max_len_k + stage - 1) / stage), shortest = (double)(older / stage + 1);
+  const double tiles = (double)((p.max_len_k + kBk - 1) / kBk);
+  const double first_block = (double)((older + std::min(255, p.max_len - 1)) / kBk + 1);
+  const long r32 = (p.max_len + kBq - 1) / kBq, r256 = (p.max_len + 255) / 256;   // of a sequence
+  const long slices = (long)p.B * p.Hq, grid = r32 * slices;
   if (grid > 16 * kNumCus) return false;
-  if (blocks <= kNumCus) return true;
-  const long shortest = (p.max_len_k - p.max_len) / stage + 1;
-  const long mean2 = p.cu ? 2 * longest : shortest + longest;   // twice the mean
-  return blocks * (mean2 + 6) <= 2l * chain * kNumCus * longest;
+  const auto ahead = [&](long n32, long n256, double cus) {
+    return c.step * launch_span(n32, shortest + 3, longest + 3, cus) + (double)(grid - n32) / kNumCus <=
+           c.first + c.tile * launch_span(n256, first_block, tiles, cus);
+  };
+  if (!p.cu) return ahead(grid, r256 * slices, kNumCus);
+  const double reach = std::min(1.0, (double)p.Hq / std::gcd(slices, 32l));
+  return ahead(std::min(grid, (long)p.Hq * (p.Nq / kBq + p.B)),
+               std::min(r256 * slices, (long)p.Hq * (p.Nq / 256 + p.B)), kNumCus) &&
+         ahead(r32 * p.Hq, r256 * p.Hq, kNumCus * reach);
+}
+
+// Measured (us, kernel of 256 rows / of 32; tau = 1e-3, D = 128 unless stated): 32 heads x 256
+// 17.8 / 10.7, x 512 28.1 / 20.5, x 1024 47.8 / 49.3, x 2048 85 / 129; 8 heads x 2048 76.8 /
+// 37.4, x 4096 136 / 106, 512 x 8192 245 / 81; D = 64, 12 x 2 heads x 1172 42.7 / 45.9, 4 x 16
+// heads x 134 7.9 / 11.2, packed 4298 + 389 + 139 + 38 tokens, 4 heads 126 / 205.  One step
+// (up to 128 keys) stays with the other kernel (64 x 64: 6.4 / 8.6).  The counters of V tiles
+// are defined by groups of 256 rows, so calls with counters stay there too.
+template <class P>
+inline bool fwd_takes_rows(const P& p, int D) {
+  return !p.counters && p.max_len_k > kRowsTiles * kBk &&
+         rows_ahead(p, D == 128 ? RowsRates{2.4, 1.32, 0.91} : RowsRates{2.4, 1.24, 0.79});
+}
+
+// Measured (us per backward, kernel of 256 rows / of 32, D = 128 GQA 8/2 unless stated): 128
+// tokens 28.7 / 25.8, 1024 119 / 84, 4096 396 / 349, 8192 833 / 875; MHA 8 heads 2048 138 / 87,
+// 32 heads 2048 238 / 298; D = 64, packed 4298 + 389 + 139 + 38 tokens, 4/2 heads 426 / 469.
+// From tau = 0.1 on the other kernel may skip for less (language-model-like at tau = 1: 2048
+// tokens 177 / 157, 4096 331 / 339).
+template <class P>
+inline bool dq_takes_rows(const P& p, int D) {
+  const bool may_skip = p.log2tau >= kSparseLog2Tau;
+  if (D == 128) return rows_ahead(p, may_skip ? RowsRates{6.0, 1.41, 0.70} : RowsRates{4.0, 1.41, 1.13});
+  return rows_ahead(p, may_skip ? RowsRates{3.0, 1.02, 0.85} : RowsRates{3.0, 1.06, 0.95});
 }
 
 }  // namespace mala

@@ -690,19 +690,8 @@ __global__ __launch_bounds__(2 * kRowsTiles * 64) void mala_fwd_rows_kernel(FwdP
   }
 }
 
-// Whether a call takes the rows kernel.  Its chain of four tiles is ~3.3 of the rows
-// kernel's steps.  Measured (D = 128, us, other kernel / rows kernel; 32 query heads unless
-// stated): 256 x 256 17.8 / 10.7, 512 x 512 28.1 / 20.5, 1024 x 1024 47.8 / 49.3, 2048 x 2048
-// 85 / 129; 8 heads 2048 x 2048 76.8 / 37.4, 4096 x 4096 136 / 106, 512 x 8192 245 / 81, 2048 x
-// 8192 246 / 149; one stage (64 x 64) 6.4 / 8.6, which stays with the other kernel.  The
-// counters of V tiles are defined by groups of 256 rows, so calls with counters stay there
-// too.
-static bool use_rows_kernel(const FwdParams& p) {
-  return !p.counters && p.max_len_k > kRowsTiles * kBk && few_row_blocks(p, 3);
-}
-
 hipError_t launch_fwd(const FwdParams& p, int D, hipStream_t st) {
-  if (use_rows_kernel(p)) {
+  if (fwd_takes_rows(p, D)) {
     dim3 grid((unsigned)((p.max_len + kBq - 1) / kBq) * p.B * p.Hq), block(2 * kRowsTiles * 64);
     if (D == 128)
       hipLaunchKernelGGL(mala_fwd_rows_kernel<128>, grid, block, 0, st, p);

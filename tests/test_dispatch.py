@@ -17,6 +17,7 @@ PROGRAM = r"""
 using namespace mala;
 struct P {
   const void* cu;
+  const void* counters;
   int B, Hq, Hkv, Nq, Nk, max_len, max_len_k, nkblk, psize, nparts;
   float log2tau;
 };
@@ -28,6 +29,7 @@ int main() {
   while (std::scanf("%d %d %d %d %d %d %d %d %d %lf", &kind, &p.B, &p.Hq, &p.Hkv, &p.Nq, &p.Nk,
                     &p.max_len, &p.max_len_k, &D, &tau) == 10) {
     p.cu = kind ? &p : nullptr;
+    p.counters = nullptr;
     p.nkblk = (p.max_len_k + kBwdKeys - 1) / kBwdKeys;
     p.log2tau = std::log2(tau);
     if (kind)
@@ -138,4 +140,37 @@ def test_dkdv_plan_of_packed_batches(tmp_path):
         (_packed([16384] * 4, 32, 8, 128, 1.0), "sequence"),
         (_packed([8192, 100], 4, 1, 128, 1.0), "pairs+parts")]
     got = _ask(tmp_path, PACKED, [x for x, _ in want])
+    assert got == [a for _, a in want]
+
+
+ROWS = """  static char s[8];
+  std::snprintf(s, sizeof(s), "%d%d", fwd_takes_rows(p, D), dq_takes_rows(p, D));
+  return s;
+"""
+
+
+def test_kernels_of_few_row_blocks(tmp_path):
+    # forward and dQ pass by 32 rows per workgroup ("1") or 256 ("0"), by measurement; unless
+    # stated, the other kernel took 3-150% longer
+    fixed = lambda *x: _fixed(x[0], x[1], x[1], *x[2:])
+    packed = lambda lens, H, *x: _packed(lens, H, H, *x)
+    want = [
+        (fixed(1, 32, 256, 256, 128, 1e-3), "11"), (fixed(1, 32, 512, 512, 128, 1e-3), "11"),
+        (fixed(1, 32, 2048, 2048, 128, 1e-3), "00"), (fixed(1, 8, 2048, 2048, 128, 1e-3), "11"),
+        (fixed(1, 8, 4096, 4096, 128, 1e-3), "11"), (fixed(1, 8, 8192, 8192, 128, 1e-3), "00"),
+        (fixed(1, 8, 512, 16384, 128, 1e-3), "11"), (fixed(1, 8, 64, 64, 128, 1e-3), "01"),
+        (fixed(1, 1, 1024, 1024, 64, 1e-3), "11"), (fixed(1, 8, 2048, 2048, 128, 1.0), "11"),
+        # more row blocks than one round of the chip, of few steps
+        (fixed(4, 16, 134, 134, 64, 1.0), "00"),    # dQ pass: a tie
+        (fixed(12, 2, 1172, 1172, 64, 1e-3), "01"),
+        (fixed(6, 4, 1135, 1376, 128, 1.0), "00"), (fixed(3, 8, 771, 13015, 128, 1.0), "00"),
+        (fixed(2, 4, 3177, 10541, 64, 1.0), "01"),
+        # the longest sequence's workgroups fall to a share of the chip
+        (packed([38, 139, 389, 4298], 4, 64, 1e-3), "00"),
+        # sequences of few rows in a grid that the longest one sizes
+        (packed([300, 1, 64, 513, 37], 4, 128, 1e-3), "11"), (packed([1000, 7, 256], 2, 64, 1.0), "11"),
+        (packed([56, 24, 3052], 8, 64, 1e-3), "11"),
+        # (dQ pass: 4% behind the other kernel)
+        (packed([21, 55, 31, 19, 164, 85, 133, 72, 491, 1610], 8, 128, 1e-3), "01")]
+    got = _ask(tmp_path, ROWS, [x for x, _ in want])
     assert got == [a for _, a in want]
