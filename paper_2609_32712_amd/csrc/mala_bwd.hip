@@ -1029,15 +1029,18 @@ __device__ __forceinline__ long uniform(long x) {
 }
 
 // The same for the sparse sequences of a call whose other sequences are the blocks kernel's.
-// A workgroup takes the items blockIdx.x, blockIdx.x + gridDim.x, ...; without a sparse
-// sequence it leaves at once, which still costs ~1.9 us of its CU (LDS holds one at a time).
-// Up to kPairsSparseGrid workgroups, ~8 per CU: with one per item, calls without a sparse
-// sequence paid 41-118 us for 4096-16384 items, 2-6% of the backward (D = 64: 4 x 4096 tokens,
-// 32 heads; packed 16384 + 3 x 64 tokens, 8 heads), now ~15; half as many leave the CUs
-// unevenly loaded (8 x 4096 language-model-like tokens at tau = 1: 520 us with one per item,
-// 529 with 2039, 544 with 1021).  An odd number, so that the parts of a block (a power of two
-// of items apart) do not fall to one workgroup (16384 such tokens: 971 us, 1470 with 1024).
-constexpr unsigned kPairsSparseGrid = 2039;
+// A workgroup takes an item of each pass over the grid; without a sparse sequence it leaves at
+// once.  The items come longest first.  Whole sweeps: every second pass goes from the last
+// workgroup to the first, so that one with a long item, whose chain can set the kernel's time
+// (an attention sink's), gets none or a short one besides (8 x 4096 language-model-like tokens
+// at tau = 1, GQA 8/2, 2048 items: backward 536 us with every pass in the same order, 529 so
+// and with one item per workgroup), and up to ~16 workgroups per CU (2 x 16384 such tokens,
+// GQA 16/4, 4096 items: 2831 us with 2039 workgroups, 2772 with 4079; 2 x 32768, 8/2: 6849 /
+// 6568).  Parts: the same order in every pass (packed 16384 + 8 shorter, forward and backward
+// 1890 us, 2031 with turns) and half as many workgroups (16384 tokens: 969 / 1050; packed 6000 x
+// 3 + 2000, 16/4: 916 / 976).  Odd numbers, so that the parts of a block (a power of two of
+// items apart) do not fall to one workgroup (16384 such tokens: 971 us, 1470 with 1024).
+constexpr unsigned kPairsSparseGrid = 4079, kPairsSparseGridParts = 2039;
 template <int D>
 __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_sparse_kernel(BwdParams p) {
   const int BHk = p.B * p.Hkv, n = kBwdKeys / kBk * p.nkblk * BHk * p.nparts;
@@ -1050,7 +1053,9 @@ __global__ __launch_bounds__(512) void mala_bwd_dkdv_pairs_sparse_kernel(BwdPara
     any |= __builtin_amdgcn_ballot_w64(b < p.B && sparse(b, seq_slice(p, b)));
   }
   if (!any) return;
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+  for (int i0 = 0, back = 0; i0 < n; i0 += gridDim.x, back ^= p.nparts == 1) {
+    const int i = i0 + (int)(back ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+    if (i >= n) continue;
     const int b = i % BHk / p.Hkv;
     Seg sg = seq_slice(p, b);
     // scalar registers, which the loads of the starts in this loop do not give by themselves
@@ -1689,7 +1694,8 @@ static void launch_bwd_t(BwdParams p, hipStream_t st) {
     hipLaunchKernelGGL((mala_bwd_dkdv_kernel<D, true>), dim3(n / p.nparts * pb.nparts), dim3(1024), 0,
                        st, pb);
     hipLaunchKernelGGL(mala_bwd_dkdv_pairs_sparse_kernel<D>,
-                       dim3(std::min(4 * n, kPairsSparseGrid)), dim3(512), 0, st, p);
+                       dim3(std::min(4 * n, p.nparts > 1 ? kPairsSparseGridParts : kPairsSparseGrid)), dim3(512),
+                       0, st, p);
   }
   if (p.nparts > 1) {
     const long slices = (long)p.B * p.Hkv, blocks = ((long)p.max_len_k * (D / 4) + 255) / 256;
