@@ -272,7 +272,7 @@ def train_workload(name, taus, reps, warmup, supp_taus=(), supp=None, memory=Tru
             "retained_tiles_pct_fwd": pct(cf[1], cf[0]),
             "retained_tiles_pct_bwd": pct(cb[1], cb[0]),
             "v_tiles_needed_pct_fwd": pct(cf[5], cf[2]),
-            "do_tiles_loaded_pct_bwd": pct(cb[2], do_dense),
+            "do_tiles_needed_pct_bwd": pct(cb[2], do_dense),
             "mean_slots_per_query_fwd": round(float(cf[3]) / rows, 1),
             "mean_slots_per_query_bwd": round(float(cb[3]) / rows, 1),
             "executed_tflops_fwd": round(fl_f / (f[0] * 1e-3) / 1e12, 1),
@@ -423,8 +423,12 @@ def mfma_probe(reps=5, blocks=256 * 12, iters=4096):
 
 
 def source_sha(path):
-    with open(path, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()[:16]
+    """Stamp of a kernel source and of the launch rules beside it."""
+    sha = hashlib.sha256()
+    for p in (path, os.path.join(os.path.dirname(path), "mala_dispatch.h")):
+        with open(p, "rb") as fh:
+            sha.update(fh.read())
+    return sha.hexdigest()[:16]
 
 
 TRAFFIC_FILES = {"bwd": "mala_bwd_traffic_128k.json", "decode": "mala_decode_traffic_128k.json"}
@@ -609,8 +613,9 @@ def summarize_skip_trace(trace_csv):
              "statistics).  tau = 1e30 skips every "
              "backward tile and every forward tile but each row's first (the cost floor of "
              "the skip path: score MFMAs, the test, staging and synchronisation); the last "
-             "column is that floor as a fraction of the dense time.  From tau = 0.1 on both "
-             "dK/dV kernels are launched and one of them leaves at once.", "",
+             "column is that floor as a fraction of the dense time.  From tau = 0.1 on a "
+             "kernel marks the sparse sequences and both dK/dV kernels are launched, each for "
+             "its own sequences.", "",
              "| kernel | tau 0 (dense) | tau 1 | tau 1e30 (all skipped) | floor / dense |",
              "|---|---|---|---|---|"]
     for k, v in sorted(dur.items(), key=lambda kv: -sum(kv[1])):
@@ -992,7 +997,7 @@ def main():
             "retained_tiles_pct_fwd": pct(rt["cf"][1], rt["cf"][0]),
             "retained_tiles_pct_bwd": pct(rt["cb"][1], rt["cb"][0]),
             "v_tiles_needed_pct_fwd": pct(rt["cf"][5], rt["cf"][2]),
-            "do_tiles_loaded_pct_bwd": pct(rt["cb"][2], do_dense),
+            "do_tiles_needed_pct_bwd": pct(rt["cb"][2], do_dense),
             "mean_slots_per_query_fwd": round(float(rt["cf"][3]) / (w.B * w.Hq * w.N), 1),
             "mean_slots_per_query_bwd": round(float(rt["cb"][3]) / (w.B * w.Hq * w.N), 1),
             "executed_tflops_fwd": round(fl_f / (rt["fwd"][0] * 1e-3) / 1e12, 1),
@@ -1036,7 +1041,7 @@ def main():
             "retained_tiles_pct_fwd": pct(cf1[1], cf1[0]),
             "retained_tiles_pct_bwd": pct(cb1[1], cb1[0]),
             "v_tiles_needed_pct_fwd": pct(cf1[5], cf1[2]),
-            "do_tiles_loaded_pct_bwd": pct(cb1[2], do_dense),
+            "do_tiles_needed_pct_bwd": pct(cb1[2], do_dense),
             "retained_head_tiles_pct_decode": pct(cd1[1], cd1[0]),
             "v_tiles_fetched_pct_decode": pct(cd1[2], k_tiles),
             "v_tiles_consumed_pct_decode": pct(cd1[5], k_tiles),

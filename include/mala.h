@@ -92,11 +92,10 @@ enum {
                                whose offline test the key-major dK/dV pass, recomputing
                                it, confirms (equal to MALA_CNT_RETAINED when the two
                                passes agree; 0 in forward and decode) */
-  MALA_CNT_V_NEEDED = 5, /* the loads of MALA_CNT_V_TILES that a retained tile used:
+  MALA_CNT_V_NEEDED = 5, /* the tiles of MALA_CNT_V_TILES that a retained tile used:
                             forward: (workgroup, key tile) pairs with a retained tile;
-                            backward: (key-major workgroup, query tile) pairs with a
-                            retained tile; decode: fetched V tiles that some head of
-                            the group retained */
+                            backward: the same as MALA_CNT_V_TILES; decode: fetched V
+                            tiles that some head of the group retained */
   MALA_CNT_SET_HASH = 6, /* fingerprint of the retained set: the sum modulo 2^64 of
                             splitmix64(b << 52 | h << 40 | i << 20 | j) over the
                             retained tiles (sequence b, query head h, query tile i,

@@ -424,9 +424,9 @@ def bwd_varlen(q, k, v, cu_seqlens, max_seqlen, o, lse, dout, scale, tau, stats=
 
 
 def default_num_splits(B, Hkv, Nk, num_cus=256, waves_per_simd=2):
-    """Splits that give about num_cus * 4 * waves_per_simd decode wavefronts (one
-    wavefront per batch x KV head x split), capped so that each split keeps at
-    least 16 tiles of 32 keys."""
+    """Splits that give about num_cus * 4 * waves_per_simd of them over batch and KV
+    heads, capped so that each keeps at least 16 tiles of 32 keys.  (One wavefront takes
+    a split, in calls of at most 256 splits a team of 4 or 8.)"""
     tiles = -(-Nk // 32)
     want = max(1, (num_cus * 4 * waves_per_simd) // max(1, B * Hkv))
     return int(max(1, min(want, tiles // 16 if tiles >= 16 else 1)))
